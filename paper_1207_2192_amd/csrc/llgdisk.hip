@@ -21,6 +21,7 @@
 
 #include "../../include/llgdisk.h"
 #include "llg_aux_kernels.hpp"
+#include "llg_spectrum.hpp"
 
 namespace llg {
 // persistent-kernel instances, one translation unit per mode (kernels_*.hip)
@@ -822,6 +823,53 @@ int scratch_ptr(int dev, unsigned char** out) {
     return 0;
 }
 
+// ---------------------------------------------------------------- power spectra
+// One workgroup per sequence (len = 2^(logm + 1) <= 2^(PS_MAX_LOGM + 1)).
+template <int LOGM = 3>
+void spectrum_whole(int logm, const double* x, int n_seq, long long bstride, long long tstride, int remove_mean,
+                    int window, double* out, hipStream_t st) {
+    if constexpr (LOGM <= PS_MAX_LOGM) {
+        if (logm != LOGM)
+            return spectrum_whole<LOGM + 1>(logm, x, n_seq, bstride, tstride, remove_mean, window, out, st);
+        hipLaunchKernelGGL(ps_whole<LOGM>, dim3(n_seq), dim3(PsShape<LOGM, 0>::THREADS), 0, st, x, bstride, tstride,
+                           remove_mean, window, out);
+    }
+}
+
+template <int LOGM2 = PS_MAX_LOGM>
+void spectrum_rows(int logm2, double2* Y, long long M, int n_seq, hipStream_t st) {
+    if constexpr (LOGM2 >= 7) {
+        if (logm2 != LOGM2) return spectrum_rows<LOGM2 - 1>(logm2, Y, M, n_seq, st);
+        hipLaunchKernelGGL(ps_rows<LOGM2>, dim3((unsigned)(M >> LOGM2), n_seq), dim3(PsShape<LOGM2, 0>::THREADS), 0,
+                           st, Y, M);
+    }
+}
+
+// Longer sequences: 2^logm = M1 x M2 complex points in two transform launches.
+void spectrum_split(int logm, const double* x, int n_seq, long long bstride, long long len, long long tstride,
+                    int remove_mean, int window, double* work, double* out, hipStream_t st) {
+    const long long M = len / 2;
+    double2* Y = reinterpret_cast<double2*>(work);   // M points per sequence, then the means
+    double* mean = work + 2 * M * n_seq;
+    // the smallest of 64, 512, 2048 that leaves rows of at most 2^PS_MAX_LOGM points
+    const int logm1 = logm - 6 <= PS_MAX_LOGM ? 6 : logm - 9 <= PS_MAX_LOGM ? 9 : 11;
+    const long long M2 = M >> logm1;
+    hipLaunchKernelGGL(ps_mean, dim3(n_seq), dim3(1024), 0, st, x, bstride, len, tstride, remove_mean, mean);
+    const dim3 threads(PsShape<6, 6>::THREADS);      // the three shapes hold the same number of points
+    if (logm1 == 6)
+        hipLaunchKernelGGL((ps_cols<6, 6>), dim3((unsigned)(M2 >> 6), n_seq), threads, 0, st, x, bstride, len, tstride,
+                           window, mean, Y);
+    else if (logm1 == 9)
+        hipLaunchKernelGGL((ps_cols<9, 3>), dim3((unsigned)(M2 >> 3), n_seq), threads, 0, st, x, bstride, len, tstride,
+                           window, mean, Y);
+    else
+        hipLaunchKernelGGL((ps_cols<11, 1>), dim3((unsigned)(M2 >> 1), n_seq), threads, 0, st, x, bstride, len, tstride,
+                           window, mean, Y);
+    spectrum_rows(logm - logm1, Y, M, n_seq, st);
+    const unsigned blocks = (unsigned)std::min<long long>((M / 2 + 256) / 256, 4096);
+    hipLaunchKernelGGL(ps_separate, dim3(blocks, n_seq), dim3(256), 0, st, Y, len, 1ll << logm1, out);
+}
+
 int check_handle(llg_disk h) {
     if (!h) return fail(LLG_EINVAL, "null handle");
     int dev = -1;
@@ -1193,23 +1241,11 @@ int llg_power_spectrum(const double* x, int n_seq, long long bstride, long long 
     if (tstride < 1 || bstride < 0) return fail(LLG_EINVAL, "need tstride >= 1 and bstride >= 0");
     if (window != 0 && window != 1) return fail(LLG_EINVAL, "window: 0 = none, 1 = Hann");
     hipStream_t st = (hipStream_t)stream;
-    double2* A = reinterpret_cast<double2*>(work);
-    double2* B = A + (size_t)len * n_seq;
-    const int half_blocks = (int)std::min<long long>((len / 2 + 255) / 256, 65535);
-    const int full_blocks = (int)std::min<long long>((len + 255) / 256, 65535);
-    hipLaunchKernelGGL(ps_mean, dim3(n_seq), dim3(256), 0, st, x, bstride, len, tstride, remove_mean, B);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(ps_load, dim3(full_blocks, n_seq), dim3(256), 0, st, x, bstride, len, tstride, window,
-                       (const double2*)B, A);
-    HIP_TRY(hipGetLastError());
-    double2* in = A;
-    double2* outb = B;
-    for (long long Ns = 1; Ns < len; Ns *= 2) {
-        hipLaunchKernelGGL(ps_pass, dim3(half_blocks, n_seq), dim3(256), 0, st, (const double2*)in, outb, len, Ns);
-        HIP_TRY(hipGetLastError());
-        std::swap(in, outb);
-    }
-    hipLaunchKernelGGL(ps_power, dim3(full_blocks, n_seq), dim3(256), 0, st, (const double2*)in, len, out);
+    const int logm = (int)std::lround(std::log2((double)len)) - 1;
+    if (logm <= PS_MAX_LOGM)
+        spectrum_whole(logm, x, n_seq, bstride, tstride, remove_mean, window, out, st);
+    else
+        spectrum_split(logm, x, n_seq, bstride, len, tstride, remove_mean, window, work, out, st);
     HIP_TRY(hipGetLastError());
     return 0;
 }
