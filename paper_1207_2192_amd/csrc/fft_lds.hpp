@@ -69,6 +69,29 @@ __device__ __forceinline__ void dft8(float2* x) {
     x[7] = csub(e3, t3);
 }
 
+// dft8 of inputs x[4 .. 7] = 0 (not read): eight complex additions fewer, which
+// the compiler may not drop by itself (x + 0 is not x for x = -0).
+template <bool INV>
+__device__ __forceinline__ void dft8_lo(float2* x) {
+    const float2 r2 = rot90<INV>(x[2]), r3 = rot90<INV>(x[3]);
+    const float2 e0 = cadd(x[0], x[2]), e2 = csub(x[0], x[2]), e1 = cadd(x[0], r2), e3 = csub(x[0], r2);
+    const float2 o0 = cadd(x[1], x[3]), o2 = csub(x[1], x[3]), o1 = cadd(x[1], r3), o3 = csub(x[1], r3);
+    const float r = 0.70710678118654752440f;
+    const float2 t1 = INV ? make_float2(r * (o1.x - o1.y), r * (o1.x + o1.y))
+                          : make_float2(r * (o1.x + o1.y), r * (o1.y - o1.x));
+    const float2 t2 = rot90<INV>(o2);
+    const float2 t3 = INV ? make_float2(-r * (o3.x + o3.y), r * (o3.x - o3.y))
+                          : make_float2(r * (o3.y - o3.x), -r * (o3.x + o3.y));
+    x[0] = cadd(e0, o0);
+    x[4] = csub(e0, o0);
+    x[1] = cadd(e1, t1);
+    x[5] = csub(e1, t1);
+    x[2] = cadd(e2, t2);
+    x[6] = csub(e2, t2);
+    x[3] = cadd(e3, t3);
+    x[7] = csub(e3, t3);
+}
+
 template <int R, bool INV>
 __device__ __forceinline__ void dftR(float2* x) {
     if constexpr (R == 2) {

@@ -25,6 +25,15 @@ struct BoolC {
     static constexpr bool value = B;
 };
 
+// Disk membership of cell (j, i) of a D x D box, in exact integer arithmetic:
+// the cell centre ((i-(D-1)/2), (j-(D-1)/2)) lies inside or on the circle of
+// radius D/2.  Same rule as the host-built mask; computed in registers so
+// that no load sits in front of the state loads.
+__device__ __forceinline__ bool in_disk(int j, int i, int D) {
+    const int x = 2 * i - (D - 1), y = 2 * j - (D - 1);
+    return x * x + y * y <= D * D;
+}
+
 // Per-disk descriptor (device memory, written once by the host).
 struct DiskDesc {
     int D, P, H, Dp;          // box, FFT size, P/2+1, D rounded up to a multiple of SB

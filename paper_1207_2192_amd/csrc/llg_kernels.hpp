@@ -27,15 +27,6 @@
 
 namespace llg {
 
-// Disk membership of cell (j, i) of a D x D box, in exact integer arithmetic:
-// the cell centre ((i-(D-1)/2), (j-(D-1)/2)) lies inside or on the circle of
-// radius D/2.  Same rule as the host-built mask; computed in registers so
-// that no load sits in front of the state loads.
-__device__ __forceinline__ bool in_disk(int j, int i, int D) {
-    const int x = 2 * i - (D - 1), y = 2 * j - (D - 1);
-    return x * x + y * y <= D * D;
-}
-
 // Rows staged in LDS per row iteration (the U row pairs and one row above and
 // below) and the padded length of a staged row (one zero margin on each side).
 template <int P, int R, int UG>

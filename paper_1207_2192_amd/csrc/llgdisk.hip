@@ -21,6 +21,7 @@
 
 #include "../../include/llgdisk.h"
 #include "llg_aux_kernels.hpp"
+#include "llg_resident.hpp"
 #include "llg_spectrum.hpp"
 
 namespace llg {
@@ -33,6 +34,7 @@ const void* persistent_kernel_heun_vjp(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_relax(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_rk4_series(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_heun_series(int UG, int RSEL, int PMAX);
+const void* resident_kernel(int mode, bool series);   // kernels_resident.hip
 }  // namespace llg
 
 using namespace llg;
@@ -189,6 +191,7 @@ struct llg_disk_s {
     int UG = 1;                       // wavefront groups per workgroup of the persistent launch
     int RSEL = 0;                     // transform policy (radix and column strategy)
     int PMAX = 256;                   // largest FFT size of the handle's disks (kernel instance)
+    bool resident = false;            // field kernel and integrators: one llg_resident workgroup per disk
     int onchip_pmax = 0;              // disks with P <= this (64 or 128; 0: none) run on one workgroup, spectra in LDS
     unsigned spin_limit = SPIN_LIMIT; // polls of a group-barrier wait before it raises ERR_BARRIER
     unsigned onchip_lds = 0;          // dynamic LDS bytes of the on-chip capable launches (largest on-chip workspace)
@@ -497,6 +500,15 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
     return 0;
 }
 
+// Whether llg_resident can step the handle.  Every disk has to be small: a mixed
+// batch would need two launches, which run one after the other on a stream.
+bool can_be_resident(llg_disk h) {
+    return std::all_of(h->P.begin(), h->P.end(), [](int P) { return P == RES_P; });
+}
+
+// Modes of llg_resident (the adjoint and relaxation kernels keep the persistent plan).
+bool resident_mode(int kmode) { return kmode == MODE_DEMAG || kmode == MODE_RK4 || kmode == MODE_HEUN; }
+
 int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int* wg_per_disk,
            const int* P_override, llg_disk* out) {
     if (!out) return fail(LLG_EINVAL, "null output handle");
@@ -599,6 +611,9 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         d.bar = h->bars + 32 * k;
     }
     if ((rc = plan(h, default_unit_groups(h), 0, wg_per_disk))) return rc;
+    // explicit workgroup counts ask for the persistent plan; otherwise small disks are resident: measured faster
+    // for one disk (RK1 us per step against RK2 on 5 workgroups) up to many (RK3)
+    h->resident = !wg_per_disk && can_be_resident(h);
     if ((rc = h->dalloc(&h->prm_dev, n))) return rc;
     if ((rc = h->dalloc(&h->hint_dev, 2 * (size_t)n))) return rc;
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->prm_pin), n * sizeof(DiskPrm), hipHostMallocDefault));
@@ -719,43 +734,49 @@ int launch(llg_disk h, int mode, float* m, float* out, long long nsteps, unsigne
            const DiskDesc* desc_override = nullptr, unsigned int* bars_override = nullptr,
            double* series = nullptr, long long every = 0) {
     const int kmode = (mode == MODE_RHS || mode == MODE_ENERGY) ? MODE_DEMAG : mode;   // kernel of the mode
-    const unsigned dyn = on_chip_instance(kmode, h->UG) ? h->onchip_lds : 0;   // on-chip spectra
-    if (!(h->plan_modes & (1u << kmode))) {
-        int cap = 0;
-        int rc = max_coresident_workgroups(h->UG, h->RSEL, h->PMAX, &cap, 1u << kmode, h->onchip_lds);
-        if (rc) return rc;
-        if (h->n_wg > cap)
-            return fail(LLG_EUNSUPPORTED, "the launch plan (" + std::to_string(h->n_wg) +
-                                              " workgroups, tuned for the integrator) exceeds what this mode keeps "
-                                              "co-resident (" + std::to_string(cap) + "); re-plan with llg_tune");
-        h->plan_modes |= 1u << kmode;   // checked once per plan
-    }
-    if (series && !(h->plan_series_modes & (1u << kmode))) {   // the series instance: its own co-residency, once per plan
-        const void* k = persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, true);
-        if (!k) return fail(LLG_EUNSUPPORTED, "no series kernel instance for this launch shape");
-        int dev = 0, ncu = 0, b = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        if (dyn) allow_dynamic_lds(k);
-        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, WG_THREADS * h->UG, dyn));
-        if (h->n_wg > ncu * b)
-            return fail(LLG_EUNSUPPORTED, "the launch plan (" + std::to_string(h->n_wg) +
-                                              " workgroups) exceeds what the series kernel keeps co-resident (" +
-                                              std::to_string(ncu * b) + "); re-plan with llg_tune");
-        h->plan_series_modes |= 1u << kmode;
-    }
-    const int nb = (h->n_bars + 255) / 256;
-    hipLaunchKernelGGL(zero_u32, dim3(nb), dim3(256), 0, st, bars_override ? bars_override : h->bars, h->n_bars);
-    HIP_TRY(hipGetLastError());
     KArgs a = make_args(h, h->prm_dev, mode, m, out, nsteps, seed, step0, replica0, step_ptr, rec, relax_x,
                         relax_out, kappa, tol, relax_cut2);
-    if (desc_override) a.disks = desc_override;
     a.series = series;
     a.every = (int)every;
     void* args[] = {&a};
-    if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
-    HIP_TRY(hipLaunchCooperativeKernel(persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, series != nullptr),
-                                       dim3(h->n_wg), dim3(WG_THREADS * h->UG), args, dyn, st));
+    const bool resident = h->resident && resident_mode(kmode);
+    if (resident) {   // workgroups independent of each other: a plain launch, no barrier counters
+        if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
+        HIP_TRY(hipLaunchKernel(resident_kernel(kmode, series != nullptr), dim3(h->n), dim3(RES_THREADS), args, 0, st));
+    } else {
+        const unsigned dyn = on_chip_instance(kmode, h->UG) ? h->onchip_lds : 0;   // on-chip spectra
+        if (!(h->plan_modes & (1u << kmode))) {
+            int cap = 0;
+            int rc = max_coresident_workgroups(h->UG, h->RSEL, h->PMAX, &cap, 1u << kmode, h->onchip_lds);
+            if (rc) return rc;
+            if (h->n_wg > cap)
+                return fail(LLG_EUNSUPPORTED, "the launch plan (" + std::to_string(h->n_wg) +
+                                                  " workgroups, tuned for the integrator) exceeds what this mode keeps "
+                                                  "co-resident (" + std::to_string(cap) + "); re-plan with llg_tune");
+            h->plan_modes |= 1u << kmode;   // checked once per plan
+        }
+        if (series && !(h->plan_series_modes & (1u << kmode))) {   // the series instance: its own co-residency, once per plan
+            const void* k = persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, true);
+            if (!k) return fail(LLG_EUNSUPPORTED, "no series kernel instance for this launch shape");
+            int dev = 0, ncu = 0, b = 0;
+            HIP_TRY(hipGetDevice(&dev));
+            HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+            if (dyn) allow_dynamic_lds(k);
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, WG_THREADS * h->UG, dyn));
+            if (h->n_wg > ncu * b)
+                return fail(LLG_EUNSUPPORTED, "the launch plan (" + std::to_string(h->n_wg) +
+                                                  " workgroups) exceeds what the series kernel keeps co-resident (" +
+                                                  std::to_string(ncu * b) + "); re-plan with llg_tune");
+            h->plan_series_modes |= 1u << kmode;
+        }
+        const int nb = (h->n_bars + 255) / 256;
+        hipLaunchKernelGGL(zero_u32, dim3(nb), dim3(256), 0, st, bars_override ? bars_override : h->bars, h->n_bars);
+        HIP_TRY(hipGetLastError());
+        if (desc_override) a.disks = desc_override;
+        if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
+        HIP_TRY(hipLaunchCooperativeKernel(persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, series != nullptr),
+                                           dim3(h->n_wg), dim3(WG_THREADS * h->UG), args, dyn, st));
+    }
     if (h->timing) {
         HIP_TRY(hipEventRecord(h->time_ev[mode][1], st));
         h->time_valid[mode] = true;
@@ -929,14 +950,16 @@ long long llg_state_size(llg_disk h) { return h ? h->state_size : fail(LLG_EINVA
 
 int llg_disk_workgroups(llg_disk h, int k) {
     if (!h || k < 0 || k >= h->n) return fail(LLG_EINVAL, "bad handle or disk index");
-    return h->G[k];
+    return h->resident ? 1 : h->G[k];
 }
 
 int llg_tune(llg_disk h, int unit_groups, int radix_policy, const int* wg_per_disk) {
     int rc = check_handle(h);
     if (rc) return rc;
     HIP_TRY(hipDeviceSynchronize());
-    return plan(h, unit_groups, radix_policy, wg_per_disk);
+    if ((rc = plan(h, unit_groups, radix_policy, wg_per_disk))) return rc;
+    h->resident = false;
+    return 0;
 }
 
 int llg_set_on_chip(llg_disk h, int max_P) {
@@ -950,6 +973,7 @@ int llg_set_on_chip(llg_disk h, int max_P) {
         h->onchip_pmax = old;   // the previous plan stays in force
         return rc;
     }
+    h->resident = false;
     return 0;
 }
 
@@ -987,8 +1011,8 @@ int llg_launch_shape(llg_disk h, int* unit_groups, int* workgroups, int* threads
     if (!h) return fail(LLG_EINVAL, "null handle");
     if (radix_policy) *radix_policy = h->RSEL;
     if (unit_groups) *unit_groups = h->UG;
-    if (workgroups) *workgroups = h->n_wg;
-    if (threads) *threads = WG_THREADS * h->UG;
+    if (workgroups) *workgroups = h->resident ? h->n : h->n_wg;
+    if (threads) *threads = h->resident ? RES_THREADS : WG_THREADS * h->UG;
     return 0;
 }
 
@@ -1025,19 +1049,21 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     std::vector<int> ocs = {0};
     if (pmin <= 64) ocs.push_back(64);
     if (pmin <= 128 && std::count_if(h->P.begin(), h->P.end(), [](int P) { return P == 128; }) > 0) ocs.push_back(128);
-    struct Cand { int UG, RSEL; double scale; int oc; };
+    struct Cand { int UG, RSEL; double scale; int oc; bool resident; };
     std::vector<Cand> cands;
     for (int ug : {1, 2, 4})
         for (int rs : {0, 1, 2, 3})
-            for (double sc : {1.0, 0.5, 0.25}) cands.push_back({ug, rs, sc, 0});
+            for (double sc : {1.0, 0.5, 0.25}) cands.push_back({ug, rs, sc, 0, false});
     for (size_t q = 1; q < ocs.size(); ++q)   // on chip: one unit group, the full workgroup budget
-        for (int rs : {0, 1, 2, 3}) cands.push_back({1, rs, 1.0, ocs[q]});
+        for (int rs : {0, 1, 2, 3}) cands.push_back({1, rs, 1.0, ocs[q], false});
+    if (can_be_resident(h)) cands.push_back({1, 0, 1.0, 0, true});
     double best = 1e300;
-    Cand bestc{h->UG, h->RSEL, 1.0, h->onchip_pmax};
+    Cand bestc{h->UG, h->RSEL, 1.0, h->onchip_pmax, h->resident};
     for (const Cand& c : cands) {
         // the tuned plan must keep the integrator and the field kernel (observables) co-resident
-        const unsigned modes = (1u << mode) | (1u << MODE_DEMAG);
+        const unsigned modes = c.resident ? ALL_MODES : (1u << mode) | (1u << MODE_DEMAG);
         h->onchip_pmax = c.oc;
+        h->resident = c.resident;
         if ((rc = plan(h, c.UG, c.RSEL, nullptr, modes, c.scale))) continue;
         float ms = 0.f;
         bool ok = true;
@@ -1061,7 +1087,9 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
         }
     }
     h->onchip_pmax = bestc.oc;
-    if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, (1u << mode) | (1u << MODE_DEMAG), bestc.scale))) return rc;
+    h->resident = bestc.resident;
+    const unsigned modes = bestc.resident ? ALL_MODES : (1u << mode) | (1u << MODE_DEMAG);
+    if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, modes, bestc.scale))) return rc;
     if (best_us) *best_us = best * 1e3 / (double)probe_steps;
     return 0;
 }
@@ -1113,6 +1141,7 @@ int llg_rk4_step_noalloc(llg_disk h, float* m, long long nsteps, const llg_param
     if ((rc = scratch_ptr(h->device, &base))) return rc;
     hipStream_t st = (hipStream_t)stream;
     if ((rc = upload_params(h, p, st))) return rc;
+    if (h->resident) return launch(h, MODE_RK4, m, nullptr, nsteps, 0, 0, 0, st);   // no workspaces at all
     hipLaunchKernelGGL(scratch_descriptors, dim3((h->n + 63) / 64), dim3(64), 0, st, h->desc_dev, h->n, base);
     HIP_TRY(hipGetLastError());
     unsigned int* bars = reinterpret_cast<unsigned int*>(base + align256((unsigned long long)h->n * sizeof(DiskDesc)));
@@ -1319,7 +1348,7 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
     zp.blockDim = dim3(256);
     zp.kernelParams = zargs;
     hipGraphNode_t nz, np, na;
-    HIP_TRY(hipGraphAddKernelNode(&nz, g->graph, nullptr, 0, &zp));
+    if (!h->resident) HIP_TRY(hipGraphAddKernelNode(&nz, g->graph, nullptr, 0, &zp));
     // node 2: the persistent cooperative launch
     const int mode = integrator == 0 ? MODE_RK4 : MODE_HEUN;
     KArgs a = make_args(h, gprm, mode, m, nullptr, nsteps, seed, 0, replica, integrator == 1 ? h->step_dev : nullptr,
@@ -1334,10 +1363,18 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
     kp.blockDim = dim3(WG_THREADS * h->UG);
     kp.sharedMemBytes = h->onchip_lds;   // on-chip spectra of the plan (the descriptors' flags)
     kp.kernelParams = pargs;
-    HIP_TRY(hipGraphAddKernelNode(&np, g->graph, &nz, 1, &kp));
-    hipKernelNodeAttrValue coop{};
-    coop.cooperative = 1;
-    HIP_TRY(hipGraphKernelNodeSetAttribute(np, hipKernelNodeAttributeCooperative, &coop));
+    if (h->resident) {   // one workgroup per disk: an ordinary node, nothing to reset
+        kp.func = const_cast<void*>(resident_kernel(mode, false));
+        kp.gridDim = dim3(h->n);
+        kp.blockDim = dim3(RES_THREADS);
+        kp.sharedMemBytes = 0;
+        HIP_TRY(hipGraphAddKernelNode(&np, g->graph, nullptr, 0, &kp));
+    } else {
+        HIP_TRY(hipGraphAddKernelNode(&np, g->graph, &nz, 1, &kp));
+        hipKernelNodeAttrValue coop{};
+        coop.cooperative = 1;
+        HIP_TRY(hipGraphKernelNodeSetAttribute(np, hipKernelNodeAttributeCooperative, &coop));
+    }
     // node 3 (Heun): advance the step counter so that the next replay continues the noise stream
     if (integrator == 1) {
         unsigned long long* sp = h->step_dev;
