@@ -130,6 +130,15 @@ long long llg_state_size(llg_disk h);
 /* Workgroups assigned to disk k (host). */
 int llg_disk_workgroups(llg_disk h, int k);
 
+/* Resident disks (the plan of a new handle whose disks all have P = 64, unless
+ * wg_per_disk was given): the field entry points and the integrators run one
+ * workgroup of 512 threads per disk that keeps the whole step loop in LDS and
+ * registers, as an ordinary launch; llg_disk_workgroups and llg_launch_shape
+ * report it.  llg_tune and llg_set_on_chip ask for the persistent launch
+ * instead, llg_autotune weighs both.  The adjoint and relaxation always use the
+ * persistent launch.  llg_demag_field, llg_rhs and llg_energy of other handles
+ * are three ordinary launches, independent of the plan. */
+
 /* Re-plan the persistent launch of h (host; synchronises the device):
  * unit_groups = 1, 2 or 4 groups of three wavefronts per workgroup (each
  * group carries one transform per field component at a time), the transform
@@ -141,7 +150,7 @@ int llg_disk_workgroups(llg_disk h, int k);
  * The plan keeps the kernels of every mode co-resident (the adjoint and
  * relaxation kernels hold fewer workgroups per CU than the integrators), so
  * explicit counts are trimmed, largest first, to that limit; llg_autotune
- * plans for its integrator and the field kernel only, and a mode launched
+ * plans for its integrator only, and a mode launched
  * later under such a plan is checked and refused if it cannot hold the plan.
  * Results do not depend on the plan beyond float rounding of the radix
  * schedule. */
@@ -151,9 +160,9 @@ int llg_tune(llg_disk h, int unit_groups, int radix_policy, const int* wg_per_di
  * with FFT size P <= max_P (64 or 128; 0 = none) is stepped by one workgroup
  * that keeps the disk's row/column spectra (3 (P/2+1) D' complex floats, D'
  * = D rounded up to 8: 25 KB at P = 64, up to 100 KB at P = 128) in its LDS
- * for the whole launch of the field kernel and the integrators, so the two
+ * for the whole launch of the integrators, so the two
  * transform phases of a field evaluation exchange them without leaving the
- * CU; the adjoint and relaxation kernels keep them in global memory, as every
+ * CU; the field, adjoint and relaxation kernels keep them in global memory, as every
  * disk of a larger P does.  Every workgroup of those launches reserves the
  * largest on-chip workspace of the handle.  The on-chip kernel instances have
  * one group of three wavefronts per workgroup.  Re-plans like llg_tune with
@@ -324,11 +333,10 @@ int llg_heun_vjp(llg_disk h, const float* rec, long long nsteps, unsigned long l
 int llg_core_position_vjp(llg_disk h, const float* m, double lambda_ex_nm, const double* core,
                           const double* rbar, float* mbar, void* stream);
 
-/* Opt-in launch timing (host): with enable set, every later persistent
- * launch of h (the field kernel, the integrators, their series, adjoint and
- * relaxation forms; not graph replays) is bracketed by two HIP events on its
- * stream, just around the cooperative kernel (after the barrier reset), kept
- * per kind of launch.  llg_last_launch_ms waits for the last launch of one
+/* Opt-in launch timing (host): with enable set, every later launch of h (the
+ * field kernels, the integrators, their series, adjoint and relaxation forms;
+ * not graph replays) is bracketed by two HIP events on its stream, just around
+ * its kernels (after the barrier reset of a persistent launch), kept per kind of launch.  llg_last_launch_ms waits for the last launch of one
  * kind (mode: 0 field, 1 right-hand side, 2 energy, 3 RK4, 4 Heun, 5 RK4
  * adjoint, 6 relaxation, 7 Heun adjoint) and returns its duration in ms;
  * LLG_EINVAL when no launch of that kind was timed since timing was

@@ -19,22 +19,26 @@ __global__ void advance_u64(unsigned long long* p, unsigned long long n) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *p += n;
 }
 
-// E = E_ex + E_demag + E_ext per disk from the per-workgroup partials, summed in
-// workgroup order (deterministic).
-__global__ void energy_finalize(const DiskDesc* disks, int n, double* out) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const DiskDesc d = disks[k];
+// E = E_ex + E_demag + E_ext per disk from the partials of its G workgroups, one
+// wavefront per disk; the order of the sums depends on G alone (deterministic).
+__global__ __launch_bounds__(64) void energy_finalize(const double* part, int G, double* out) {
+    const int k = blockIdx.x;
+    const double* p = part + (size_t)k * G * PART_STRIDE;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int g = 0; g < d.G; ++g) {
-        s0 += d.part[g * PART_STRIDE + 0];
-        s1 += d.part[g * PART_STRIDE + 1];
-        s2 += d.part[g * PART_STRIDE + 2];
+    for (int g = threadIdx.x; g < G; g += 64) {
+        s0 += p[g * PART_STRIDE + 0];
+        s1 += p[g * PART_STRIDE + 1];
+        s2 += p[g * PART_STRIDE + 2];
     }
-    out[4 * k + 0] = s0 + s1 + s2;
-    out[4 * k + 1] = s0;
-    out[4 * k + 2] = s1;
-    out[4 * k + 3] = s2;
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (threadIdx.x == 0) {
+        out[4 * k + 0] = s0 + s1 + s2;
+        out[4 * k + 1] = s0;
+        out[4 * k + 2] = s1;
+        out[4 * k + 3] = s2;
+    }
 }
 
 // Adjoint parameter gradients: pgrad[2k] += alpha_bar, pgrad[2k+1] += c_bar of disk k,
@@ -88,26 +92,52 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     return s;
 }
 
-// <m> per disk, float64.
-__global__ __launch_bounds__(OBS_THREADS) void mean_kernel(const DiskDesc* disks, const float* m_base, double* out) {
+// <m> per disk, float64: block (s, k) sums the rows [s rows, (s + 1) rows) of
+// disk k, mean_finish adds the strips.  A disk that is one strip is finished at
+// once.  (One block per disk read the 0.75 MB of a D = 250 disk alone: 150 us
+// for 64 of them, bound by the loads one CU keeps in flight; strips of 16 rows
+// take 13 + 3 us.  Up to D = 96 one block is faster than a second launch: 9.5 us
+// against 11.8 from call to call.)
+__global__ __launch_bounds__(OBS_THREADS) void mean_kernel(const DiskDesc* disks, const float* m_base, int rows,
+                                                           int n_strips, double* part, double* out) {
     __shared__ double sh[OBS_THREADS / 64];
-    const DiskDesc d = disks[blockIdx.x];
-    const int DD = d.D * d.D;
-    const float* m = m_base + d.m_off;
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    for (int c = threadIdx.x; c < DD; c += OBS_THREADS)
-        if (d.mask[c]) {
-            sx += m[c];
-            sy += m[DD + c];
-            sz += m[2 * DD + c];
+    const int k = blockIdx.y, strip = blockIdx.x;
+    const DiskDesc d = disks[k];
+    const int D = d.D, DD = D * D, j0 = strip * rows;
+    if (j0 >= D) return;
+    const float* m = m_base + d.m_off + j0 * D;
+    const int n = min(rows, D - j0) * D;
+    double sum[3] = {0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int q = threadIdx.x; q < n; q += OBS_THREADS) {
+        const int j = q / D;
+        if (in_disk(j0 + j, q - j * D, D)) {
+            sum[0] += m[q];
+            sum[1] += m[DD + q];
+            sum[2] += m[2 * DD + q];
         }
-    sx = block_sum(sx, sh);
-    sy = block_sum(sy, sh);
-    sz = block_sum(sz, sh);
-    if (threadIdx.x == 0) {
-        out[3 * blockIdx.x + 0] = sx / d.n_cells;
-        out[3 * blockIdx.x + 1] = sy / d.n_cells;
-        out[3 * blockIdx.x + 2] = sz / d.n_cells;
+    }
+    const bool whole = D <= rows;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double s = block_sum(sum[c], sh);
+        if (threadIdx.x == 0) {
+            if (whole)
+                out[3 * k + c] = s / d.n_cells;
+            else
+                part[((size_t)k * n_strips + strip) * 3 + c] = s;
+        }
+    }
+}
+
+__global__ __launch_bounds__(64) void mean_finish(const DiskDesc* disks, int rows, int n_strips,
+                                                  const double* part, double* out) {
+    const int k = blockIdx.x, D = disks[k].D;
+    if (D <= rows) return;
+    const int ns = (D + rows - 1) / rows;   // at most 16
+    for (int c = 0; c < 3; ++c) {
+        const double s = wave_sum((int)threadIdx.x < ns ? part[((size_t)k * n_strips + threadIdx.x) * 3 + c] : 0.0);
+        if (threadIdx.x == 0) out[3 * k + c] = s / disks[k].n_cells;
     }
 }
 
@@ -120,11 +150,13 @@ __global__ __launch_bounds__(OBS_THREADS) void mean_kernel(const DiskDesc* disks
 // taken in float32 first; only when a raw difference lies within
 // CORE_WRAP_MARGIN of +-pi (where float32 rounding could flip the wrap) is the
 // plaquette recomputed with float64 angles, so every decision equals the
-// float64 one.  The block writes its count of +1 plaquettes and its best
-// candidate (score: closeness to the hint, else the sum of m_z^2 over the
-// corners; ties to the lower plaquette index) to part[k][s].
+// float64 one.  The strip's angles are taken once per cell into LDS (a cell is a
+// corner of four plaquettes; 64 replicas of R = 250 nm: 33 -> 25 us).  The block
+// writes its count of +1 plaquettes and its best candidate (score: closeness to
+// the hint, else the sum of m_z^2 over the corners; ties to the lower plaquette
+// index) to part[k][s].
 // core_finish_kernel: one block per disk picks r_v from the strips (same
-// order), then forms the m_z^2-weighted centroid over the disk cells within
+// rule), then forms the m_z^2-weighted centroid over the disk cells within
 // the cutoff of r_v (scanning only the cutoff's bounding box) or, without a
 // +1 plaquette, over the whole disk.  float64 throughout the reductions.
 constexpr int CORE_ROWS = 8;
@@ -144,11 +176,11 @@ __device__ __forceinline__ double wrap_pi(double x) {
     return t - pi;
 }
 
-// Winding of the plaquette with corners a, b, c, d (counter-clockwise).
-__device__ __forceinline__ int plaquette_winding(const float* mx, const float* my, int ca, int cb, int cc, int cd) {
+// Winding of the plaquette with corners a, b, c, d (counter-clockwise), from the
+// float32 angles fa .. fd; the state is read again only for the float64 recheck.
+__device__ __forceinline__ int plaquette_winding(float fa, float fb, float fc, float fd, const float* mx,
+                                                 const float* my, int ca, int cb, int cc, int cd) {
     const float pi_f = 3.14159265358979f;
-    const float fa = atan2f(my[ca], mx[ca]), fb = atan2f(my[cb], mx[cb]);
-    const float fc = atan2f(my[cc], mx[cc]), fd = atan2f(my[cd], mx[cd]);
     const float r0 = fb - fa, r1 = fc - fb, r2 = fd - fc, r3 = fa - fd;
     const float lo = pi_f - CORE_WRAP_MARGIN, hi = pi_f + CORE_WRAP_MARGIN;
     auto near_pi = [&](float r) {
@@ -171,23 +203,28 @@ __device__ __forceinline__ bool core_better(double s, int i, double bs, int bi) 
     return s > bs || (s == bs && i < bi);
 }
 
-// hint: per disk (x, y) in nm, NaN = no hint.
+// hint: per disk (x, y) in nm, NaN = no hint; null = none for any disk.
 __global__ __launch_bounds__(OBS_THREADS) void core_scan_kernel(const DiskDesc* disks, const float* m_base,
                                                                 const double* hint, double a_nm, int n_strips,
                                                                 CorePart* part) {
     __shared__ double s_score[OBS_THREADS / 64];
     __shared__ int s_idx[OBS_THREADS / 64], s_cnt[OBS_THREADS / 64];
+    __shared__ float ang[(CORE_ROWS + 1) * (MAX_P / 2)];
     const int k = blockIdx.y, strip = blockIdx.x;
     const DiskDesc d = disks[k];
     const int D = d.D, DD = D * D, Dm = D - 1;
     const float* m = m_base + d.m_off;
     const double half = (D - 1) / 2.0;
-    const double hx = hint[2 * k], hy = hint[2 * k + 1];
+    const double hx = hint ? hint[2 * k] : NAN, hy = hint ? hint[2 * k + 1] : NAN;
     const bool use_hint = !(isnan(hx) || isnan(hy));
     const int j0 = strip * CORE_ROWS, j1 = min(j0 + CORE_ROWS, Dm);
     double best = -INFINITY;
     int best_idx = 0x7fffffff, nplus = 0;
     const int nrow = j1 > j0 ? j1 - j0 : 0;
+    if (nrow > 0)
+        for (int q = threadIdx.x; q < (nrow + 1) * D; q += OBS_THREADS)
+            ang[q] = atan2f(m[DD + j0 * D + q], m[j0 * D + q]);
+    __syncthreads();
     for (int q = threadIdx.x; q < nrow * Dm; q += OBS_THREADS) {
         const int j = j0 + q / Dm, i = q % Dm;
         const int x0 = 2 * i - (D - 1), y0 = 2 * j - (D - 1);   // doubled centre coordinates of cell (j, i)
@@ -197,7 +234,8 @@ __global__ __launch_bounds__(OBS_THREADS) void core_scan_kernel(const DiskDesc* 
               x0 * x0 + y1 * y1 <= DD2))
             continue;
         const int ca = j * D + i, cb = ca + 1, cc = ca + D + 1, cd = ca + D;
-        if (plaquette_winding(m, m + DD, ca, cb, cc, cd) != 1) continue;
+        const float* f = ang + (j - j0) * D + i;
+        if (plaquette_winding(f[0], f[1], f[D + 1], f[D], m, m + DD, ca, cb, cc, cd) != 1) continue;
         ++nplus;
         const int p = j * Dm + i;
         double score;
@@ -254,25 +292,35 @@ __global__ __launch_bounds__(OBS_THREADS) void core_finish_kernel(const DiskDesc
     const int D = d.D, DD = D * D, Dm = D - 1;
     const float* m = m_base + d.m_off;
     const double half = (D - 1) / 2.0;
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {   // one strip per lane (at most 32)
         double bs = -INFINITY;
         int bi = 0x7fffffff, np = 0;
-        const int ns = (Dm + CORE_ROWS - 1) / CORE_ROWS;
-        for (int s = 0; s < ns; ++s) {
-            const CorePart c = part[k * n_strips + s];
-            np += c.count;
-            if (c.count > 0 && core_better(c.score, c.idx, bs, bi)) {
+        if ((int)threadIdx.x < (Dm + CORE_ROWS - 1) / CORE_ROWS) {
+            const CorePart c = part[k * n_strips + threadIdx.x];
+            np = c.count;
+            if (c.count > 0) {
                 bs = c.score;
                 bi = c.idx;
             }
         }
-        s_found = np;
-        s_xv = NAN;
-        s_yv = NAN;
-        if (np > 0) {
-            const int j = bi / Dm, i = bi - j * Dm;
-            s_xv = ((double)i - half) + 0.5;
-            s_yv = ((double)j - half) + 0.5;
+        for (int o = 32; o > 0; o >>= 1) {
+            const double os = __shfl_xor(bs, o, 64);
+            const int oi = __shfl_xor(bi, o, 64);
+            np += __shfl_xor(np, o, 64);
+            if (core_better(os, oi, bs, bi)) {
+                bs = os;
+                bi = oi;
+            }
+        }
+        if (threadIdx.x == 0) {
+            s_found = np;
+            s_xv = NAN;
+            s_yv = NAN;
+            if (np > 0) {
+                const int j = bi / Dm, i = bi - j * Dm;
+                s_xv = ((double)i - half) + 0.5;
+                s_yv = ((double)j - half) + 0.5;
+            }
         }
     }
     __syncthreads();

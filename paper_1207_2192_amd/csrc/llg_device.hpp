@@ -10,6 +10,7 @@ namespace llg {
 
 constexpr int WG_THREADS = 192;   // one group of three wavefronts: components x, y, z (or packed row pairs)
 constexpr int MAX_UG = 4;         // wavefront groups per workgroup
+constexpr int NXCD = 8;           // workgroup w of a launch runs on XCD w mod NXCD
 constexpr int MAX_P = 512;
 constexpr int MAX_R = 8;
 constexpr int LDS_FFT = 3 * 64 * MAX_R * 9 / 8 + 3 * 4 * 32;   // float2 per group: 3 waves x (64/Tf units) x padded P, bank skew
@@ -119,18 +120,33 @@ enum Mode : int {
     MODE_HEUN = 4,
     MODE_RK4_VJP = 5,
     MODE_RELAX = 6,
-    MODE_HEUN_VJP = 7
+    MODE_HEUN_VJP = 7,
+    // kernels of a single field evaluation (llg_field): MODE_DEMAG, MODE_RHS and
+    // MODE_ENERGY are chosen at run time by the last of the three
+    MODE_FIELD_ROWS = 8,
+    MODE_FIELD_COLS = 9,
+    MODE_FIELD_OUT = 10
 };
+constexpr bool field_mode(int mode) { return mode >= MODE_FIELD_ROWS; }
+
+// Unit groups of a workgroup and transform policy of the field kernels (phase 0
+// rows, 1 columns, 2 outputs) where every CU gets several tiles.  The row pass
+// carries four row pairs, so that it writes whole 64-byte segments of the
+// spectra (64 disks of R = 250 nm: 32 us; one pair at a time 82 us); the others
+// are faster with several narrow workgroups per CU (columns 55 us against 74,
+// outputs 47-76 us against 54-81 with four unit groups).
+constexpr int field_wide_ug(int phase, int PMAX) { return phase != 0 ? 1 : PMAX >= 512 ? 4 : 2; }
+constexpr int FIELD_WIDE_POL = 3;
 
 constexpr int PART_STRIDE = 8;  // doubles of per-workgroup partial sums
 
-// Kernel instances that can keep a small disk's spectra in LDS: the field
-// kernel and the integrators, with one group of three wavefronts per
-// workgroup (wider workgroups would carry the extra code path at a higher
-// register count in every plan, where it is never the faster choice); the
-// adjoint and relaxation kernels always use the workspace in global memory,
-// which every disk keeps.
-constexpr bool on_chip_mode(int mode) { return mode == MODE_DEMAG || mode == MODE_RK4 || mode == MODE_HEUN; }
+// Kernel instances that can keep a small disk's spectra in LDS: the
+// integrators, with one group of three wavefronts per workgroup (wider
+// workgroups would carry the extra code path at a higher register count in
+// every plan, where it is never the faster choice); the field, adjoint and
+// relaxation kernels always use the workspace in global memory, which every
+// disk keeps.
+constexpr bool on_chip_mode(int mode) { return mode == MODE_RK4 || mode == MODE_HEUN; }
 constexpr bool on_chip_instance(int mode, int UG) { return on_chip_mode(mode) && UG == 1; }
 
 enum ErrBits : int { ERR_BARRIER = 1, ERR_NONFINITE = 2 };
@@ -148,6 +164,8 @@ struct KArgs {
     const unsigned long long* step_ptr;   // if set, the Heun step index is read here instead of step0
     unsigned int replica0;
     int mode;
+    int field_g;          // workgroups per disk of a field kernel
+    double* part;         // energy partial sums of a field evaluation [disk][workgroups of a disk][PART_STRIDE]
     int* err;
     // constrained relaxation
     const double* relax_x;  // target vortex position per disk (2 doubles, units of a from the centre)
@@ -303,20 +321,25 @@ constexpr int OOB = (int)0x80000000u;
 __device__ __forceinline__ float bld1c(__amdgpu_buffer_rsrc_t r, int off) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
+template <int CP = CP_DEVICE>
 __device__ __forceinline__ float bld1(__amdgpu_buffer_rsrc_t r, int off) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, CP_DEVICE));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, CP));
 }
+template <int CP = CP_DEVICE>
 __device__ __forceinline__ float2 bld2(__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, CP_DEVICE));
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, CP));
 }
+template <int CP = CP_DEVICE>
 __device__ __forceinline__ float4 bld4(__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, CP_DEVICE));
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, CP));
 }
+template <int CP = CP_DEVICE>
 __device__ __forceinline__ void bst2(__amdgpu_buffer_rsrc_t r, int off, float2 v) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, CP_DEVICE);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, CP);
 }
+template <int CP = CP_DEVICE>
 __device__ __forceinline__ void bst4(__amdgpu_buffer_rsrc_t r, int off, float4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, CP_DEVICE);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, CP);
 }
 
 // Wait until every store this wave issued has completed (s_waitcnt vmcnt(0):

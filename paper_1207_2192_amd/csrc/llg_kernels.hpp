@@ -66,12 +66,16 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     constexpr int HR = RowTile<P, R, UG>::HR, HW = RowTile<P, R, UG>::HW;
 
     for (int i = tid<OPQ>(); i < P; i += NT) ltw[i] = ldg2(d.tw + i);
-    for (int r = tid<OPQ>(); r < 3 * HR; r += NT) {
-        halo[r * HW] = 0.f;
-        halo[r * HW + HW - 1] = 0.f;
-    }
+    if constexpr (MODE != MODE_FIELD_ROWS && MODE != MODE_FIELD_COLS)   // those stage no rows
+        for (int r = tid<OPQ>(); r < 3 * HR; r += NT) {
+            halo[r * HW] = 0.f;
+            halo[r * HW + HW - 1] = 0.f;
+        }
     __syncthreads();
 
+    // Shared buffers are exchanged inside a launch, except by the field kernels,
+    // whose exchanges are the launches themselves: normal cached accesses there.
+    constexpr int CP = field_mode(MODE) ? 0 : CP_DEVICE;
     float* const m = a.m + d.m_off;
     float* const out = a.out ? a.out + d.m_off : nullptr;
     const unsigned char* __restrict__ mask = d.mask;
@@ -86,27 +90,27 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
         if constexpr (ONCHIP)
             return (unsigned)off < s_bytes ? sdyn[off >> 3] : make_float2(0.f, 0.f);
         else
-            return bld2(Srs, off);
+            return bld2<CP>(Srs, off);
     };
     auto sld4 = [&](int off) -> float4 {
         if constexpr (ONCHIP)
             return (unsigned)off < s_bytes ? reinterpret_cast<const float4*>(sdyn)[off >> 4]
                                            : make_float4(0.f, 0.f, 0.f, 0.f);
         else
-            return bld4(Srs, off);
+            return bld4<CP>(Srs, off);
     };
     auto sst2 = [&](int off, float2 v) {
         if constexpr (ONCHIP) {
             if ((unsigned)off < s_bytes) sdyn[off >> 3] = v;
         } else {
-            bst2(Srs, off, v);
+            bst2<CP>(Srs, off, v);
         }
     };
     auto sst4 = [&](int off, float4 v) {
         if constexpr (ONCHIP) {
             if ((unsigned)off < s_bytes) reinterpret_cast<float4*>(sdyn)[off >> 4] = v;
         } else {
-            bst4(Srs, off, v);
+            bst4<CP>(Srs, off, v);
         }
     };
     if constexpr (ONCHIP) {   // rows no pass writes read as zeros, as in the cleared workspace
@@ -125,36 +129,36 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     const int n_rb = (d.n_pairs + U - 1) / U;
     const int n_cb_split = (H + U - 1) / U;       // column tiles of U columns (one wave per component)
     unsigned int epoch = 0;
-    // the field kernel serves demag / rhs / energy at run time; the integrators are compiled per mode
-    const int mode = (MODE == MODE_DEMAG) ? a.mode : MODE;
+    // the field kernels serve demag / rhs / energy at run time; the integrators are compiled per mode
+    const int mode = (MODE == MODE_FIELD_OUT) ? a.mode : MODE;
     // first Heun step index: from the handle's device counter when one is given
     const unsigned long long step0 = (MODE == MODE_HEUN && a.step_ptr) ? *gbl(a.step_ptr) : a.step0;
 
-    // ---- packed rows of a state into LDS (masked), columns [0, D)
+    // ---- packed rows of a state into LDS (masked), columns [0, D): every load is
+    // issued before the first use (cells outside the disk read as zero)
     auto load_state_rows = [&](int b, const float* src) {
-        for (int idx = tid<OPQ>(); idx < U * D; idx += NT) {
-            const int uu = idx / D, i = idx - uu * D;
-            const int p = b * U + uu, j0 = 2 * p, j1 = j0 + 1;
-            float x0 = 0.f, y0 = 0.f, z0 = 0.f, x1 = 0.f, y1 = 0.f, z1 = 0.f;
-            if (p < d.n_pairs) {
-                const int c0 = j0 * D + i;
-                if (in_disk(j0, i, D)) {
-                    x0 = ld_sh(src + c0);
-                    y0 = ld_sh(src + DD + c0);
-                    z0 = ld_sh(src + 2 * DD + c0);
-                }
-                if (j1 < D) {
-                    const int c1 = j1 * D + i;
-                    if (in_disk(j1, i, D)) {
-                        x1 = ld_sh(src + c1);
-                        y1 = ld_sh(src + DD + c1);
-                        z1 = ld_sh(src + 2 * DD + c1);
-                    }
-                }
+        constexpr int C = P / 2, IL = (U * C + NT - 1) / NT;   // columns of a row (D <= P/2), items per thread
+        const __amdgpu_buffer_rsrc_t Mr = make_rsrc(src, (unsigned)(3 * DD) * 4u);
+        float v[IL][2][3];
+#pragma unroll
+        for (int q = 0; q < IL; ++q) {
+            const int idx = tid<OPQ>() + q * NT, uu = idx / C, i = idx % C;
+            const int j0 = 2 * (b * U + uu);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const bool ok = uu < U && j0 + r < D && i < D && in_disk(j0 + r, i, D);
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    v[q][r][c] = bld1<CP>(Mr, ok ? (c * DD + (j0 + r) * D + i) * 4 : OOB);
             }
-            BUF(0, uu)[padb(i)] = make_float2(x0, y0);
-            BUF(1, uu)[padb(i)] = make_float2(x1, y1);
-            BUF(2, uu)[padb(i)] = make_float2(z0, z1);
+        }
+#pragma unroll
+        for (int q = 0; q < IL; ++q) {
+            const int idx = tid<OPQ>() + q * NT, uu = idx / C, i = idx % C;
+            if (uu >= U) continue;
+            BUF(0, uu)[padb(i)] = make_float2(v[q][0][0], v[q][0][1]);
+            BUF(1, uu)[padb(i)] = make_float2(v[q][1][0], v[q][1][1]);
+            BUF(2, uu)[padb(i)] = make_float2(v[q][0][2], v[q][1][2]);
         }
         __syncthreads();
     };
@@ -297,7 +301,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     };
     auto column_pass_slot = [&]() {
         stage_twiddles<P, R>(stw, ltw, t);
-        if constexpr (P == 512) {
+        if constexpr (P == 512 && !field_mode(MODE)) {
             for (int base = 0; base < H; base += G * NSLOT) {
                 const int kx = base + slot * G + g;
                 if (kx < H) column_item(kx);
@@ -499,7 +503,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             const int c = row / HR, rr = row - c * HR;
             const int j = 2 * b * U - 1 + rr;
             const bool ok = row < 3 * HR && i < D && j >= 0 && j < D && (!MASKED || in_disk(j, i, D));
-            hv[q] = bld1(Yr, ok ? (c * DD + j * D + i) * 4 : OOB);
+            hv[q] = bld1<CP>(Yr, ok ? (c * DD + j * D + i) * 4 : OOB);
         }
     };
     auto halo_load = [&](int b, const float* Ys, float (&hv)[IH], bool masked) {
@@ -1338,25 +1342,31 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
         }
         write_partials(e_ex, e_dm, 0.0);
         return;
+    } else if constexpr (MODE == MODE_FIELD_ROWS) {
+        for (int b = g; b < n_rb; b += G) {
+            load_state_rows(b, m);
+            row_forward_store(b);
+        }
+    } else if constexpr (MODE == MODE_FIELD_COLS) {
+        column_pass();
+    } else if constexpr (MODE == MODE_FIELD_OUT) {
+        for (int b = g; b < n_rb; b += G) {
+            float hv[IH];
+            SRow sv[IS];
+            if (mode != MODE_DEMAG) halo_load_t(BoolC<true>{}, b, m, hv);   // the stencil's rows
+            row_load(b, sv);
+            if (mode != MODE_DEMAG) halo_store(hv);
+            row_unpack_inverse(sv);
+            cell_update(b, 0, 0, nullptr);
+        }
+        if (mode == MODE_ENERGY) write_partials(e_ex, e_dm, e_ext);
     } else {
-        // field evaluation and integrators: the row spectra of the input state first
+        // integrators: the row spectra of the input state first
         for (int b = g; b < n_rb; b += G) {
             load_state_rows(b, m);
             row_forward_store(b);
         }
         if (!group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
-
-        // one row iteration of a field evaluation: issue every load, then stage, transform and update
-        auto row_step = [&](int b, int s, long long n, const float* Ys, float* Yn) {
-            float hv[IH];
-            SRow sv[IS];
-            halo_load(b, Ys, hv, true);
-            gather(b, s);
-            row_load(b, sv);
-            halo_store(hv);
-            row_unpack_inverse(sv);
-            cell_update(b, s, n, Yn);
-        };
 
         // all row iterations of a stage: the staged rows and row spectra of the
         // next iteration are loaded after the cell update of the current one, so
@@ -1388,54 +1398,47 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             }
         };
 
-        if constexpr (MODE == MODE_DEMAG) {
-            column_pass();
-            if (!group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
-            for (int b = g; b < n_rb; b += G) row_step(b, 0, 0, m, nullptr);
-            if (mode == MODE_ENERGY) write_partials(e_ex, e_dm, e_ext);
-        } else {
-            constexpr int nst = (MODE == MODE_RK4) ? 4 : 2;
-            for (long long n = 0; n < a.nsteps; ++n) {
-                for (int s = 0; s < nst; ++s) {
-                    column_pass();
-                    if (!group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
-                    set_field(pr.tau0 + ((double)n + stage_frac(nst, s)) * pr.dtau_d);
-                    const bool last = (n == a.nsteps - 1) && (s == nst - 1);
-                    // state whose field is evaluated (Ys) and where the next stage state goes (Yn)
-                    const float* Ys;
-                    float* Yn;
-                    if (nst == 4) {
-                        Ys = (s == 0) ? m : (s == 2) ? d.yb : d.ya;
-                        Yn = (s == 3) ? m : (s == 1) ? d.yb : d.ya;
-                    } else {
-                        Ys = (s == 0) ? m : d.ya;
-                        Yn = (s == 0) ? d.ya : m;
-                    }
-                    const bool sampled = SERIES && s == 0 && n % a.every == 0;
-                    if (sampled) {
-                        if (tid<OPQ>() < 3 * UG * 4) red4[tid<OPQ>() >> 2][tid<OPQ>() & 3] = 0.0;
-                        __syncthreads();
-                    }
-                    row_pass(s, n, Ys, Yn, !last, sampled);
-                    if (sampled) {   // this workgroup's sums of the sample into its partial slots 4..7
-                        __syncthreads();
-                        if (tid<OPQ>() < 4) {
-                            const int q = tid<OPQ>();
-                            double acc = 0.0;
-                            for (int w = 0; w < 3 * UG; ++w) acc += red4[w][q];
-                            st_shd(d.part + g * PART_STRIDE + 4 + q, acc);
-                        }
-                    }
-                    if (!last && !group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
-                    // stage 0 is never the last stage: every workgroup's partials of a
-                    // sample are visible here; workgroup 0 sums them in workgroup order
-                    if (sampled && g == 0 && tid<OPQ>() < 4) {
+        constexpr int nst = (MODE == MODE_RK4) ? 4 : 2;
+        for (long long n = 0; n < a.nsteps; ++n) {
+            for (int s = 0; s < nst; ++s) {
+                column_pass();
+                if (!group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
+                set_field(pr.tau0 + ((double)n + stage_frac(nst, s)) * pr.dtau_d);
+                const bool last = (n == a.nsteps - 1) && (s == nst - 1);
+                // state whose field is evaluated (Ys) and where the next stage state goes (Yn)
+                const float* Ys;
+                float* Yn;
+                if (nst == 4) {
+                    Ys = (s == 0) ? m : (s == 2) ? d.yb : d.ya;
+                    Yn = (s == 3) ? m : (s == 1) ? d.yb : d.ya;
+                } else {
+                    Ys = (s == 0) ? m : d.ya;
+                    Yn = (s == 0) ? d.ya : m;
+                }
+                const bool sampled = SERIES && s == 0 && n % a.every == 0;
+                if (sampled) {
+                    if (tid<OPQ>() < 3 * UG * 4) red4[tid<OPQ>() >> 2][tid<OPQ>() & 3] = 0.0;
+                    __syncthreads();
+                }
+                row_pass(s, n, Ys, Yn, !last, sampled);
+                if (sampled) {   // this workgroup's sums of the sample into its partial slots 4..7
+                    __syncthreads();
+                    if (tid<OPQ>() < 4) {
                         const int q = tid<OPQ>();
                         double acc = 0.0;
-                        for (int gg = 0; gg < G; ++gg) acc += ld_shd(d.part + gg * PART_STRIDE + 4 + q);
-                        const long long smp = n / a.every;
-                        gbl(a.series)[(smp * a.n_disks + d.k) * 4 + q] = q < 3 ? acc / (double)d.n_cells : acc;
+                        for (int w = 0; w < 3 * UG; ++w) acc += red4[w][q];
+                        st_shd(d.part + g * PART_STRIDE + 4 + q, acc);
                     }
+                }
+                if (!last && !group_barrier(d.bar, ++epoch * G, G, a.err, a.spin_limit)) return;
+                // stage 0 is never the last stage: every workgroup's partials of a
+                // sample are visible here; workgroup 0 sums them in workgroup order
+                if (sampled && g == 0 && tid<OPQ>() < 4) {
+                    const int q = tid<OPQ>();
+                    double acc = 0.0;
+                    for (int gg = 0; gg < G; ++gg) acc += ld_shd(d.part + gg * PART_STRIDE + 4 + q);
+                    const long long smp = n / a.every;
+                    gbl(a.series)[(smp * a.n_disks + d.k) * 4 + q] = q < 3 ? acc / (double)d.n_cells : acc;
                 }
             }
         }
@@ -1459,8 +1462,7 @@ constexpr bool column_slots(int POL, int MODE) {
 
 // One persistent kernel per (workgroup shape UG, transform policy POL, mode,
 // largest FFT size PMAX of the handle, observable series SER): each instance
-// carries only the code and registers of its own path.  MODE_DEMAG stands for
-// the field kernel (demag, rhs and energy, chosen at run time).
+// carries only the code and registers of its own path.
 template <int UG, int POL>
 constexpr int halo_floats(int PMAX) {
     int n = RowTile<64, Radix<64, POL>::value, UG>::floats;
@@ -1535,6 +1537,48 @@ const void* persistent_instance(int UG, int POL, int PMAX) {
     }
 #undef LLG_INST
     return nullptr;
+}
+
+// ---------------------------------------------------------------- field evaluation
+// One field evaluation (demag, right-hand side or energy) as three ordinary
+// launches: rows forward, columns, rows inverse with the outputs.  The two
+// exchanges of the spectra are the launch boundaries, so no workgroup waits for
+// another: a cooperative launch with two group barriers cost 20 us on top of a
+// kernel of 12-17 us for one disk (launches of this kind follow each other
+// every 2-3 us), and its grid was held to what one round keeps co-resident.
+// Workgroup g of G of disk k takes the tiles g, g + G, ...; with eight disks or
+// more, all workgroups of a disk run on one XCD (workgroup w on XCD w mod 8),
+// whose L2 then holds the lines that neighbouring tiles share.
+template <int UG, int POL, int MODE, int PMAX>
+__global__ __launch_bounds__(WG_THREADS* UG) __attribute__((amdgpu_waves_per_eu(3))) void llg_field(KArgs a) {
+    __shared__ float2 lds[LDS_FFT * UG];
+    __shared__ float2 ltw[MAX_P];
+    __shared__ float halo[halo_floats<UG, POL>(PMAX)];
+    const int G = a.field_g, w = blockIdx.x;
+    const bool xcd = a.n_disks >= NXCD;
+    const int k = xcd ? w % NXCD + NXCD * (w / (NXCD * G)) : w / G, g = xcd ? w / NXCD % G : w % G;
+    if (k >= a.n_disks) return;
+    DiskDesc d = a.disks[k];
+    d.G = G;
+    if constexpr (MODE == MODE_FIELD_OUT) d.part = a.part + (size_t)k * G * PART_STRIDE;
+    const DiskPrm pr = a.prm[k];
+    constexpr bool L = PMAX >= 512, SL = column_slots(POL, MODE);
+#define LLG_SIZE(p)                                                                                              \
+    case p:                                                                                                      \
+        run_disk<p, Radix<p, POL>::value, UG, MODE, L, SL, false, false>(a, d, pr, g, lds, ltw, halo, nullptr); \
+        break;
+    switch (d.P) {
+        LLG_SIZE(64)
+        LLG_SIZE(128)
+        LLG_SIZE(256)
+        case 512:
+            if constexpr (PMAX >= 512)
+                run_disk<512, Radix<512, POL>::value, UG, MODE, L, SL, false, false>(a, d, pr, g, lds, ltw, halo,
+                                                                                     nullptr);
+            break;
+        default: break;
+    }
+#undef LLG_SIZE
 }
 
 }  // namespace llg

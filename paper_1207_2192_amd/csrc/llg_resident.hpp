@@ -383,9 +383,7 @@ void llg_resident(KArgs a) {
         if (mode == MODE_ENERGY) {
             wave_sums(e3, 3);
             __syncthreads();
-            // the plan's other workgroups of this disk contribute nothing
-            for (int e = tid; e < 3 * d.G; e += RES_THREADS)
-                gbl(d.part)[(e / 3) * PART_STRIDE + e % 3] = e < 3 ? total(e) : 0.0;
+            if (tid < 3) gbl(a.part)[k * PART_STRIDE + tid] = total(tid);
         }
     } else {
         for (long long n = 0; n < a.nsteps; ++n) {

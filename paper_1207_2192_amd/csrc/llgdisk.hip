@@ -26,7 +26,6 @@
 
 namespace llg {
 // persistent-kernel instances, one translation unit per mode (kernels_*.hip)
-const void* persistent_kernel_field(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_rk4(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_heun(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_vjp(int UG, int RSEL, int PMAX);
@@ -34,6 +33,7 @@ const void* persistent_kernel_heun_vjp(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_relax(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_rk4_series(int UG, int RSEL, int PMAX);
 const void* persistent_kernel_heun_series(int UG, int RSEL, int PMAX);
+const void* field_kernel(int phase, bool wide, int PMAX);   // kernels_field.hip
 const void* resident_kernel(int mode, bool series);   // kernels_resident.hip
 }  // namespace llg
 
@@ -186,11 +186,16 @@ struct llg_disk_s {
     unsigned long long* step_dev = nullptr;   // Heun step counter (LLG_STEP_COUNTER)
     CorePart* core_part = nullptr;    // per disk and plaquette-row strip: core-position candidates
     int core_strips = 1;              // strips per disk in core_part
+    double* mean_part = nullptr;      // <m> partial sums [disk][mean_strips][3]
+    int mean_rows = 1, mean_strips = 1;   // rows of a strip, strips per disk
     unsigned plan_modes = 0;          // modes whose co-residency the current plan was checked for
     unsigned plan_series_modes = 0;   // the same for the series instances of the integrators
     int UG = 1;                       // wavefront groups per workgroup of the persistent launch
     int RSEL = 0;                     // transform policy (radix and column strategy)
     int PMAX = 256;                   // largest FFT size of the handle's disks (kernel instance)
+    bool field_wide = false;          // field kernels: shape for many tiles per CU
+    int field_g[3] = {1, 1, 1};       // their workgroups per disk (rows, columns, outputs)
+    double* field_part = nullptr;     // energy partial sums [disk][field_g[2]][PART_STRIDE]
     bool resident = false;            // field kernel and integrators: one llg_resident workgroup per disk
     int onchip_pmax = 0;              // disks with P <= this (64 or 128; 0: none) run on one workgroup, spectra in LDS
     unsigned spin_limit = SPIN_LIMIT; // polls of a group-barrier wait before it raises ERR_BARRIER
@@ -262,12 +267,11 @@ const void* persistent_kernel(int mode, int UG, int RSEL, int PMAX, bool series 
         case MODE_HEUN: return persistent_kernel_heun(UG, RSEL, PMAX);
         case MODE_RK4_VJP: return persistent_kernel_vjp(UG, RSEL, PMAX);
         case MODE_HEUN_VJP: return persistent_kernel_heun_vjp(UG, RSEL, PMAX);
-        case MODE_RELAX: return persistent_kernel_relax(UG, RSEL, PMAX);
-        default: return persistent_kernel_field(UG, RSEL, PMAX);
+        default: return persistent_kernel_relax(UG, RSEL, PMAX);
     }
 }
 
-constexpr unsigned ALL_MODES = (1u << MODE_DEMAG) | (1u << MODE_RK4) | (1u << MODE_HEUN) | (1u << MODE_RK4_VJP) |
+constexpr unsigned ALL_MODES = (1u << MODE_RK4) | (1u << MODE_HEUN) | (1u << MODE_RK4_VJP) |
                                (1u << MODE_HEUN_VJP) | (1u << MODE_RELAX);
 
 // Largest on-chip spectra workspace: P = 128, D' = 64 (3 x 65 x 64 complex floats).
@@ -284,15 +288,14 @@ void allow_dynamic_lds(const void* k) {
 }
 
 // Workgroups of the given shape that the kernels of every mode in `modes` (bit
-// mask) can keep co-resident; the field and integrator kernels carry
-// `onchip_lds` bytes of dynamic LDS (the spectra of on-chip disks).
+// mask) can keep co-resident; the integrator kernels carry `onchip_lds` bytes of dynamic LDS (the spectra of on-chip disks).
 int max_coresident_workgroups(int UG, int RSEL, int PMAX, int* out, unsigned modes = ALL_MODES,
                               unsigned onchip_lds = 0) {
     int dev = 0, ncu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     int per_cu = 1 << 30;
-    for (int mode : {MODE_DEMAG, MODE_RK4, MODE_HEUN, MODE_RK4_VJP, MODE_HEUN_VJP, MODE_RELAX}) {
+    for (int mode : {MODE_RK4, MODE_HEUN, MODE_RK4_VJP, MODE_HEUN_VJP, MODE_RELAX}) {
         if (!(modes & (1u << mode))) continue;
         const void* k = persistent_kernel(mode, UG, RSEL, PMAX);
         if (!k) return fail(LLG_EUNSUPPORTED, "no kernel instance for this launch shape");
@@ -420,7 +423,6 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
 
     // Disks whose workgroups all fit one XCD stay on one XCD (workgroup w runs
     // on XCD w mod 8); larger disks take consecutive ids and span the XCDs.
-    constexpr int NXCD = 8;
     std::vector<int> w2d, w2l;
     {
         std::vector<std::vector<std::pair<int, int>>> lanes(NXCD);
@@ -498,6 +500,32 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
     if (!h->desc_dev && (rc = h->dalloc(&h->desc_dev, n))) return rc;
     HIP_TRY(hipMemcpy(h->desc_dev, h->desc.data(), n * sizeof(DiskDesc), hipMemcpyHostToDevice));
     return 0;
+}
+
+// Launch shape of the field kernels (llg_field): one tile per workgroup while
+// the tiles of policy 0 (one transform per wavefront and component) fit one
+// round of co-resident workgroups, where latency counts; beyond, the wide
+// shapes with several tiles per workgroup.
+void plan_field(llg_disk h) {
+    constexpr int ROUND = 1024, MOST = 2048;   // workgroups of one round (4 per CU), and of a wide launch
+    auto tiles = [&](int phase, int UG, int RSEL) {   // largest count of any disk, and the sum over the disks
+        int most = 1;
+        long long total = 0;
+        for (int k = 0; k < h->n; ++k) {
+            const int U = units_per_wg(h->P[k], UG, RSEL);
+            const int items = phase == 1 ? h->P[k] / 2 + 1 : (h->D[k] + 1) / 2;
+            const int C = phase == 1 && (RSEL & 2) ? 3 * U : U, t = (items + C - 1) / C;
+            most = std::max(most, t);
+            total += t;
+        }
+        return std::make_pair(most, total);
+    };
+    h->field_wide = std::max(tiles(0, 1, 0).second, tiles(1, 1, 0).second) > ROUND;
+    for (int phase = 0; phase < 3; ++phase) {
+        const int ug = h->field_wide ? field_wide_ug(phase, h->PMAX) : 1;
+        const int most = tiles(phase, ug, h->field_wide ? FIELD_WIDE_POL : 0).first;
+        h->field_g[phase] = h->field_wide ? std::min(most, std::max(1, (MOST + h->n - 1) / h->n)) : most;
+    }
 }
 
 // Whether llg_resident can step the handle.  Every disk has to be small: a mixed
@@ -584,6 +612,9 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         for (int D : h->D) dmax = std::max(dmax, D);
         h->core_strips = std::max(1, (dmax - 1 + CORE_ROWS - 1) / CORE_ROWS);
         if ((rc = h->dalloc(&h->core_part, (size_t)n * h->core_strips))) return rc;
+        h->mean_rows = dmax <= 96 ? dmax : 16;
+        h->mean_strips = (dmax + h->mean_rows - 1) / h->mean_rows;
+        if ((rc = h->dalloc(&h->mean_part, (size_t)n * h->mean_strips * 3))) return rc;
     }
     HIP_TRY(hipMemset(h->step_dev, 0, sizeof(unsigned long long)));
     h->desc.assign(n, DiskDesc{});
@@ -611,8 +642,10 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         d.bar = h->bars + 32 * k;
     }
     if ((rc = plan(h, default_unit_groups(h), 0, wg_per_disk))) return rc;
-    // explicit workgroup counts ask for the persistent plan; otherwise small disks are resident: measured faster
-    // for one disk (RK1 us per step against RK2 on 5 workgroups) up to many (RK3)
+    plan_field(h);
+    if ((rc = h->dalloc(&h->field_part, (size_t)n * h->field_g[2] * PART_STRIDE))) return rc;
+    // explicit workgroup counts ask for the persistent plan; otherwise small disks are resident (R = 30 nm: one disk
+    // 16.2 us per RK4 step against 27.8 on 5 workgroups, 64 disks 10.1 us per Heun step against 17.6 on 128)
     h->resident = !wg_per_disk && can_be_resident(h);
     if ((rc = h->dalloc(&h->prm_dev, n))) return rc;
     if ((rc = h->dalloc(&h->hint_dev, 2 * (size_t)n))) return rc;
@@ -719,6 +752,8 @@ KArgs make_args(llg_disk h, const DiskPrm* prm, int mode, float* m, float* out, 
     a.step_ptr = step_ptr;
     a.replica0 = replica0;
     a.mode = mode;
+    a.field_g = 0;
+    a.part = h->field_part;
     a.err = h->err_dev;
     a.series = nullptr;
     a.every = 0;
@@ -743,6 +778,15 @@ int launch(llg_disk h, int mode, float* m, float* out, long long nsteps, unsigne
     if (resident) {   // workgroups independent of each other: a plain launch, no barrier counters
         if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
         HIP_TRY(hipLaunchKernel(resident_kernel(kmode, series != nullptr), dim3(h->n), dim3(RES_THREADS), args, 0, st));
+    } else if (kmode == MODE_DEMAG) {
+        if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
+        const int disks = h->n >= NXCD ? (h->n + NXCD - 1) / NXCD * NXCD : h->n;   // whole rounds of XCDs
+        for (int phase = 0; phase < 3; ++phase) {
+            a.field_g = h->field_g[phase];
+            const int ug = h->field_wide ? field_wide_ug(phase, h->PMAX) : 1;
+            HIP_TRY(hipLaunchKernel(field_kernel(phase, h->field_wide, h->PMAX), dim3(disks * a.field_g),
+                                    dim3(WG_THREADS * ug), args, 0, st));
+        }
     } else {
         const unsigned dyn = on_chip_instance(kmode, h->UG) ? h->onchip_lds : 0;   // on-chip spectra
         if (!(h->plan_modes & (1u << kmode))) {
@@ -1060,8 +1104,7 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     double best = 1e300;
     Cand bestc{h->UG, h->RSEL, 1.0, h->onchip_pmax, h->resident};
     for (const Cand& c : cands) {
-        // the tuned plan must keep the integrator and the field kernel (observables) co-resident
-        const unsigned modes = c.resident ? ALL_MODES : (1u << mode) | (1u << MODE_DEMAG);
+        const unsigned modes = c.resident ? ALL_MODES : 1u << mode;   // the plan keeps the integrator co-resident
         h->onchip_pmax = c.oc;
         h->resident = c.resident;
         if ((rc = plan(h, c.UG, c.RSEL, nullptr, modes, c.scale))) continue;
@@ -1088,7 +1131,7 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     }
     h->onchip_pmax = bestc.oc;
     h->resident = bestc.resident;
-    const unsigned modes = bestc.resident ? ALL_MODES : (1u << mode) | (1u << MODE_DEMAG);
+    const unsigned modes = bestc.resident ? ALL_MODES : 1u << mode;
     if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, modes, bestc.scale))) return rc;
     if (best_us) *best_us = best * 1e3 / (double)probe_steps;
     return 0;
@@ -1420,7 +1463,8 @@ int llg_energy(llg_disk h, const float* m, const llg_params* p, double* out, voi
     hipStream_t st = (hipStream_t)stream;
     if ((rc = upload_params(h, p, st))) return rc;
     if ((rc = launch(h, MODE_ENERGY, const_cast<float*>(m), nullptr, 0, 0, 0, 0, st))) return rc;
-    hipLaunchKernelGGL(energy_finalize, dim3((h->n + 63) / 64), dim3(64), 0, st, h->desc_dev, h->n, out);
+    hipLaunchKernelGGL(energy_finalize, dim3(h->n), dim3(64), 0, st, h->field_part, h->resident ? 1 : h->field_g[2],
+                       out);
     HIP_TRY(hipGetLastError());
     return 0;
 }
@@ -1432,12 +1476,14 @@ int llg_vortex_core_position(llg_disk h, const float* m, double lambda_ex_nm, co
     if (!m || !out) return fail(LLG_EINVAL, "null array");
     if (!(lambda_ex_nm > 0)) return fail(LLG_EINVAL, "lambda_ex must be positive");
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(hipEventSynchronize(h->hint_event));
-    for (int k = 0; k < 2 * h->n; ++k) h->hint_pin[k] = hint_nm ? hint_nm[k] : NAN;
-    HIP_TRY(hipMemcpyAsync(h->hint_dev, h->hint_pin, 2 * h->n * sizeof(double), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipEventRecord(h->hint_event, st));
+    if (hint_nm) {   // without hints nothing is staged, and no call waits for the copy of the one before
+        HIP_TRY(hipEventSynchronize(h->hint_event));
+        for (int k = 0; k < 2 * h->n; ++k) h->hint_pin[k] = hint_nm[k];
+        HIP_TRY(hipMemcpyAsync(h->hint_dev, h->hint_pin, 2 * h->n * sizeof(double), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipEventRecord(h->hint_event, st));
+    }
     hipLaunchKernelGGL(core_scan_kernel, dim3(h->core_strips, h->n), dim3(OBS_THREADS), 0, st, h->desc_dev, m,
-                       h->hint_dev, h->a_nm, h->core_strips, h->core_part);
+                       hint_nm ? h->hint_dev : nullptr, h->a_nm, h->core_strips, h->core_part);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(core_finish_kernel, dim3(h->n), dim3(OBS_THREADS), 0, st, h->desc_dev, m, h->a_nm,
                        4.0 * lambda_ex_nm / h->a_nm, h->core_strips, h->core_part, out);
@@ -1449,8 +1495,15 @@ int llg_mean_m(llg_disk h, const float* m, double* out, void* stream) {
     int rc = check_handle(h);
     if (rc) return rc;
     if (!m || !out) return fail(LLG_EINVAL, "null array");
-    hipLaunchKernelGGL(mean_kernel, dim3(h->n), dim3(OBS_THREADS), 0, (hipStream_t)stream, h->desc_dev, m, out);
+    hipStream_t st = (hipStream_t)stream;
+    hipLaunchKernelGGL(mean_kernel, dim3(h->mean_strips, h->n), dim3(OBS_THREADS), 0, st, h->desc_dev, m, h->mean_rows,
+                       h->mean_strips, h->mean_part, out);
     HIP_TRY(hipGetLastError());
+    if (h->mean_strips > 1) {
+        hipLaunchKernelGGL(mean_finish, dim3(h->n), dim3(64), 0, st, h->desc_dev, h->mean_rows, h->mean_strips,
+                           h->mean_part, out);
+        HIP_TRY(hipGetLastError());
+    }
     return 0;
 }
 
