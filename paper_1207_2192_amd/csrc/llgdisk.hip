@@ -181,7 +181,7 @@ struct llg_disk_s {
     int* wg2local = nullptr;
     int n_wg = 0;
     unsigned int* bars = nullptr;
-    int n_bars = 0;
+    int n_bars = 0;                   // words of the current plan's counters
     int* err_dev = nullptr;
     unsigned long long* step_dev = nullptr;   // Heun step counter (LLG_STEP_COUNTER)
     CorePart* core_part = nullptr;    // per disk and plaquette-row strip: core-position candidates
@@ -483,8 +483,12 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
     HIP_TRY(hipMemcpy(h->wg2disk, w2d.data(), w2d.size() * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(h->wg2local, w2l.data(), w2l.size() * sizeof(int), hipMemcpyHostToDevice));
     h->n_wg = (int)w2d.size();
+    h->n_bars = 0;
     for (int k = 0; k < n; ++k) {
         DiskDesc& d = h->desc[k];
+        d.bar = h->bars + h->n_bars;
+        d.bar_lines = bar_lines_for(G[k]);
+        h->n_bars += d.bar_lines * BAR_STRIDE;
         h->dfree(d.part);
         d.part = nullptr;
         if ((rc = h->dalloc(&d.part, (size_t)PART_STRIDE * G[k]))) return rc;
@@ -602,8 +606,8 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
 
     // ---- per-disk workspaces
     int rc = 0;
-    h->n_bars = n * 32;  // one 128-byte line per disk
-    if ((rc = h->dalloc(&h->bars, h->n_bars))) return rc;
+    // room for any plan (a graph keeps using the counters of its own)
+    if ((rc = h->dalloc(&h->bars, (size_t)n * BAR_LINES * BAR_STRIDE))) return rc;
     if ((rc = h->dalloc(&h->err_dev, 1))) return rc;
     HIP_TRY(hipMemset(h->err_dev, 0, sizeof(int)));
     if ((rc = h->dalloc(&h->step_dev, 1))) return rc;
@@ -639,7 +643,6 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         d.spec = g.spec;
         d.mask = g.mask;
         d.tw = h->twiddles[d.P];
-        d.bar = h->bars + 32 * k;
     }
     if ((rc = plan(h, default_unit_groups(h), 0, wg_per_disk))) return rc;
     plan_field(h);
@@ -813,8 +816,8 @@ int launch(llg_disk h, int mode, float* m, float* out, long long nsteps, unsigne
                                                   std::to_string(ncu * b) + "); re-plan with llg_tune");
             h->plan_series_modes |= 1u << kmode;
         }
-        const int nb = (h->n_bars + 255) / 256;
-        hipLaunchKernelGGL(zero_u32, dim3(nb), dim3(256), 0, st, bars_override ? bars_override : h->bars, h->n_bars);
+        const int n_bars = bars_override ? h->n * BAR_STRIDE : h->n_bars, nb = (n_bars + 255) / 256;
+        hipLaunchKernelGGL(zero_u32, dim3(nb), dim3(256), 0, st, bars_override ? bars_override : h->bars, n_bars);
         HIP_TRY(hipGetLastError());
         if (desc_override) a.disks = desc_override;
         if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
@@ -846,7 +849,7 @@ void* g_scratch_ptr[MAX_DEVICES] = {};
 
 __host__ __device__ inline unsigned long long align256(unsigned long long b) { return (b + 255ull) & ~255ull; }
 __host__ __device__ inline unsigned long long scratch_head(int n) {
-    return align256((unsigned long long)n * sizeof(DiskDesc)) + align256((unsigned long long)n * 32 * sizeof(unsigned));
+    return align256((unsigned long long)n * sizeof(DiskDesc)) + align256((unsigned long long)n * BAR_STRIDE * sizeof(unsigned));
 }
 __host__ __device__ inline unsigned long long scratch_disk_bytes(int D, int H, int Dp, int G) {
     const unsigned long long st = align256((unsigned long long)3 * D * D * sizeof(float));
@@ -870,7 +873,8 @@ __global__ void scratch_descriptors(const DiskDesc* src, int n, unsigned char* b
     d.aux = nullptr;
     d.S = reinterpret_cast<float2*>(p + 3 * st);
     d.part = reinterpret_cast<double*>(p + 3 * st + align256((unsigned long long)3 * d.H * d.Dp * sizeof(float2)));
-    d.bar = reinterpret_cast<unsigned int*>(base + align256((unsigned long long)n * sizeof(DiskDesc))) + 32 * k;
+    d.bar = reinterpret_cast<unsigned int*>(base + align256((unsigned long long)n * sizeof(DiskDesc))) + BAR_STRIDE * k;
+    d.bar_lines = 1;   // one 128-byte line per disk here
     reinterpret_cast<DiskDesc*>(base)[k] = d;
 }
 
