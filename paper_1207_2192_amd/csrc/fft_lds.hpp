@@ -112,6 +112,68 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Twiddled butterfly (a, b) <- (a + w b, a - w b), with conj w for the inverse:
+// six fused operations, the difference taken as 2 a - (a + w b), where a complex
+// product and two additions take eight.
+template <bool INV>
+__device__ __forceinline__ void bfly(float2& a, float2& b, float2 w) {
+    const float wy = INV ? -w.y : w.y;
+    const float2 p = make_float2(fmaf(-wy, b.y, fmaf(w.x, b.x, a.x)), fmaf(wy, b.x, fmaf(w.x, b.y, a.y)));
+    b = make_float2(fmaf(2.f, a.x, -p.x), fmaf(2.f, a.y, -p.y));
+    a = p;
+}
+// the same with -i w (forward) or i conj w (inverse)
+template <bool INV>
+__device__ __forceinline__ void bfly_i(float2& a, float2& b, float2 w) {
+    const float2 p = INV ? make_float2(fmaf(w.y, b.x, fmaf(-w.x, b.y, a.x)), fmaf(w.y, b.y, fmaf(w.x, b.x, a.y)))
+                         : make_float2(fmaf(w.y, b.x, fmaf(w.x, b.y, a.x)), fmaf(w.y, b.y, fmaf(-w.x, b.x, a.y)));
+    b = make_float2(fmaf(2.f, a.x, -p.x), fmaf(2.f, a.y, -p.y));
+    a = p;
+}
+
+// Twiddles of a fused radix-8 stage at one position: the inputs x_j carry w^j.  The
+// factors are moved into the butterflies of the decimated radix-2 steps, which
+// need w, w^2, w^4 and w W8 only (W8 = exp(-i pi / 4)).
+struct Twiddle8 {
+    float2 w1, w2, w4, w8;
+};
+__device__ __forceinline__ Twiddle8 make_twiddle8(float2 w1) {
+    const float r = 0.70710678118654752440f;
+    const float2 w2 = cmul(w1, w1);
+    return {w1, w2, cmul(w2, w2), make_float2(r * (w1.x + w1.y), r * (w1.y - w1.x))};
+}
+
+// x_k <- sum_j x_j w^j exp(-+2 pi i j k / 8): 72 vector operations against 80 for
+// seven products and a plain transform, and 12 against 24 for the twiddles, which
+// every row transform makes anew, but chains of three dependent ones per step.
+// Faster where three wavefronts share a SIMD (the 64 replicas of R = 250 nm,
+// P = 512: 281.4 -> 278 us per Heun step), slower where a wavefront waits for
+// itself (ragged ensemble, P <= 256: 357 -> 366 us per RK4 step), no different in
+// the resident kernel (P = 64): fft_run takes it at P = 512 only.
+template <bool INV>
+__device__ __forceinline__ void fused_dft8(float2* x, const Twiddle8& t) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bfly<INV>(x[j], x[j + 4], t.w4);
+    float2 e0 = x[0], e2 = x[2], e1 = x[4], e3 = x[6];   // E0, E2 from the sums, E1, E3 from the differences
+    float2 o0 = x[1], o2 = x[3], o1 = x[5], o3 = x[7];
+    bfly<INV>(e0, e2, t.w2);
+    bfly_i<INV>(e1, e3, t.w2);
+    bfly<INV>(o0, o2, t.w2);
+    bfly_i<INV>(o1, o3, t.w2);
+    bfly<INV>(e0, o0, t.w1);
+    bfly<INV>(e1, o1, t.w8);
+    bfly_i<INV>(e2, o2, t.w1);
+    bfly_i<INV>(e3, o3, t.w8);
+    x[0] = e0;
+    x[1] = e1;
+    x[2] = e2;
+    x[3] = e3;
+    x[4] = o0;
+    x[5] = o1;
+    x[6] = o2;
+    x[7] = o3;
+}
+
 // Powers w^1 .. w^(R-1) of one table twiddle by products of powers (at most
 // three roundings deep for R = 8), so that a stage reads one twiddle from LDS
 // instead of R-1.
@@ -157,19 +219,28 @@ constexpr bool fft_whole_radix() {
 // depend only on the lane's position t in its transform, so a lane that runs
 // many transforms computes them once (w[s-1][j-1] = w_s^j).
 template <int P, int R>
+constexpr bool fft_fused() { return P == 512 && R == 8; }
+template <int P, int R>
 struct StageTwiddles {
     static constexpr int NFULL = ilog2(P) / ilog2(R);
-    float2 w[NFULL > 1 ? NFULL - 1 : 1][R - 1];
+    static constexpr bool fused = fft_fused<P, R>();
+    float2 w[fused ? 1 : NFULL > 1 ? NFULL - 1 : 1][R - 1];
+    Twiddle8 f[fused ? NFULL - 1 : 1];
 };
 template <int P, int R>
 __device__ __forceinline__ void stage_twiddles(StageTwiddles<P, R>& st, const float2* tw, int t) {
     int Ns = R;
 #pragma unroll
     for (int s = 1; s < StageTwiddles<P, R>::NFULL; ++s) {
-        float2 w[R];
-        twiddle_powers<R>(tw[(t & (Ns - 1)) * (P / (Ns * R))], w);
+        const float2 w1 = tw[(t & (Ns - 1)) * (P / (Ns * R))];
+        if constexpr (fft_fused<P, R>()) {
+            st.f[s - 1] = make_twiddle8(w1);
+        } else {
+            float2 w[R];
+            twiddle_powers<R>(w1, w);
 #pragma unroll
-        for (int j = 1; j < R; ++j) st.w[s - 1][j - 1] = w[j];
+            for (int j = 1; j < R; ++j) st.w[s - 1][j - 1] = w[j];
+        }
         Ns *= R;
     }
 }
@@ -190,24 +261,36 @@ __device__ __forceinline__ void fft_run(float2 (&v)[R], float2* buf, const float
     int Ns = 1;
 #pragma unroll
     for (int s = 0; s < NFULL; ++s) {
-        if (s > 0) {
+        if constexpr (fft_fused<P, R>()) {
+            if (s > 0) {
 #pragma unroll
-            for (int j = 0; j < R; ++j) v[j] = buf[padb(t + j * Tf)];
-            float2 w[R];
-            if (st) {
-#pragma unroll
-                for (int j = 1; j < R; ++j) w[j] = st->w[s - 1][j - 1];
+                for (int j = 0; j < R; ++j) v[j] = buf[padb(t + j * Tf)];
+                fused_dft8<INV>(v, st ? st->f[s - 1] : make_twiddle8(tw[(t & (Ns - 1)) * (P / (Ns * R))]));
+            } else if constexpr (ZHI) {
+                dft8_lo<INV>(v);
             } else {
-                const int kk = t & (Ns - 1);
-                twiddle_powers<R>(tw[kk * (P / (Ns * R))], w);
+                dft8<INV>(v);
             }
+        } else {
+            if (s > 0) {
 #pragma unroll
-            for (int j = 1; j < R; ++j) v[j] = INV ? cmulc(v[j], w[j]) : cmul(v[j], w[j]);
-        } else if constexpr (ZHI) {
+                for (int j = 0; j < R; ++j) v[j] = buf[padb(t + j * Tf)];
+                float2 w[R];
+                if (st) {
 #pragma unroll
-            for (int j = R / 2; j < R; ++j) v[j] = make_float2(0.f, 0.f);
+                    for (int j = 1; j < R; ++j) w[j] = st->w[s - 1][j - 1];
+                } else {
+                    const int kk = t & (Ns - 1);
+                    twiddle_powers<R>(tw[kk * (P / (Ns * R))], w);
+                }
+#pragma unroll
+                for (int j = 1; j < R; ++j) v[j] = INV ? cmulc(v[j], w[j]) : cmul(v[j], w[j]);
+            } else if constexpr (ZHI) {
+#pragma unroll
+                for (int j = R / 2; j < R; ++j) v[j] = make_float2(0.f, 0.f);
+            }
+            dftR<R, INV>(v);
         }
-        dftR<R, INV>(v);
         if (KEEP && s == NFULL - 1) break;
         const int kk = t & (Ns - 1);
         const int base = (t - kk) * R + kk;
