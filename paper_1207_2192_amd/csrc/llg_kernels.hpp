@@ -42,10 +42,11 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                                          float2* lds, float2* ltw, float* halo, float2* sdyn) {
     constexpr int Tf = P / R;
     constexpr int U = UG * (64 / Tf);          // transforms per component in flight per workgroup
-    // the adjoint keeps many values per cell in registers, the P = 512 kernels (LARGE) run
-    // at higher occupancy, and four-group workgroups carry four tiles at once: recompute
+    // the adjoint and the relaxation keep many values per cell in registers, the P = 512
+    // kernels (LARGE) run at higher occupancy, and four-group workgroups carry four tiles at once: recompute
     // their index arithmetic inside the loop instead of holding it in registers
-    constexpr bool OPQ = MODE == MODE_RK4_VJP || MODE == MODE_HEUN_VJP || LARGE || UG != 2;
+    constexpr bool OPQ =
+        MODE == MODE_RK4_VJP || MODE == MODE_HEUN_VJP || MODE == MODE_RELAX || LARGE || UG != 2;
     constexpr int NT = WG_THREADS * UG;
     constexpr int H = P / 2 + 1;
     const int D = d.D, Dp = d.Dp, G = d.G;
@@ -520,6 +521,24 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             if (row < 3 * HR && i < HC) halo[row * HW + 1 + i] = hv[q];
         }
     };
+    // Staged values of component c around column i of row pair uu: rows j0 - 1 .. j0 + 2
+    // of the column and the left and right neighbours of rows j0 and j0 + 1.
+    struct Sten {
+        float col[4], lft[2], rgt[2];
+        __device__ __forceinline__ float sum(int r) const { return col[r] + col[r + 2] + lft[r] + rgt[r]; }
+    };
+    auto stencil = [&](int c, int uu, int i) {
+        Sten q;
+        const float* hr = halo + (c * HR + 2 * uu) * HW + 1 + i;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q.col[r] = hr[r * HW];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            q.lft[r] = hr[(r + 1) * HW - 1];
+            q.rgt[r] = hr[(r + 1) * HW + 1];
+        }
+        return q;
+    };
 
     double e_ex = 0.0, e_dm = 0.0, e_ext = 0.0;
     const float cf = pr.c, al = pr.alpha, dt = pr.dtau;
@@ -831,6 +850,66 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     //   alpha_bar += kb . (-Y x (Y x b)),   c_bar += bbar . (h + H).
     // The slope cotangents follow RK4 backwards: kb_4 = dt/6 yb', kb_3 = dt/3 yb' + dt Ybar_4,
     // kb_2 = dt/3 yb' + dt/2 Ybar_3, kb_1 = dt/6 yb' + dt/2 Ybar_2;  yb = yb' + sum Ybar.
+    // Per row iteration the rows of bbar and of the recorded state and the row spectra
+    // are loaded together; the direct part, the accumulator, the recorded demag fields
+    // of both stages and the step's cotangent of each cell are in flight during the
+    // inverse transforms.  (Loads where they were used, each behind a branch: 15.5 us a
+    // stage for a lone R = 80 nm disk, 14.7 now; lone R = 250 nm 27 -> 24, and the
+    // registers now allow twice the workgroups.)
+    struct VGath {
+        float ax[2][3], ac[2][3], hf[2][3], hs[2][3], y[2][3];
+        float Y[2][3], Yx[2][3];   // recorded state and its neighbour sum
+    };
+    VGath vg[IC];
+    // recorded state and exchange sum of this thread's cells, through the staging buffer
+    // (which the rows of bbar take afterwards)
+    auto record_stencil = [&](const float (&hY)[IH]) {
+        halo_store(hY);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < IC; ++q) {
+            int uu, i;
+            if (!cell_item(tid<OPQ>() + q * NT, uu, i)) continue;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const Sten y = stencil(c, uu, i);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    vg[q].Y[r][c] = y.col[r + 1];
+                    vg[q].Yx[r][c] = y.sum(r);
+                }
+            }
+        }
+        __syncthreads();
+    };
+    const unsigned st_bytes = (unsigned)(3 * DD) * 4u;
+    struct CellSrc {
+        __amdgpu_buffer_rsrc_t ax, ac, hf, hs, y;
+    };
+    auto cell_load = [&](int b, int q, int r, const CellSrc& S) {   // row r of this thread's item q
+        int uu, i;
+        const bool item = cell_item(tid<OPQ>() + q * NT, uu, i);
+        const int j = 2 * (b * U + uu) + r;
+        const bool ok = item && j < D;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int o = ok ? (c * DD + j * D + i) * 4 : OOB;
+            vg[q].ax[r][c] = bld1c(S.ax, o);
+            vg[q].ac[r][c] = bld1c(S.ac, o);
+            vg[q].hf[r][c] = bld1c(S.hf, o);
+            vg[q].hs[r][c] = bld1c(S.hs, o);
+            vg[q].y[r][c] = bld1(S.y, o);
+        }
+    };
+    auto cell_loads = [&](int b, const CellSrc& S) {
+#pragma unroll
+        for (int q = 0; q < IC; ++q)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) cell_load(b, q, r, S);
+    };
+    // the cells' loads fly over the inverse transforms where the registers hold both; else
+    // a cell's values are loaded where they are used
+    constexpr bool EARLY = R < 8 || UG < 4;
     auto vjp_update = [&](int b, long long k, long long K) {
         const long long N = a.nsteps;
         const bool fin = k > 0, sta = k < K;
@@ -838,51 +917,39 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
         const int sf = fin ? 3 - (int)((k - 1) % 4) : 0, ss = sta ? 3 - (int)(k % 4) : 0;
         const float* Bf = ((k - 1) & 1) ? d.yb : d.ya;      // bbar of the finishing stage
         float* Bs = (k & 1) ? d.yb : d.ya;                  // bbar of the starting stage
-        const GLOBAL_AS float* Yrec = gbl(recd) + ((size_t)(ns * 4 + ss) * 2) * 3 * DD;
-        const GLOBAL_AS float* Hrec = Yrec + 3 * DD;
-        const GLOBAL_AS float* Hfin = gbl(recd) + ((size_t)(nf * 4 + sf) * 2 + 1) * 3 * DD;
+        const float* Yrec = recd + ((size_t)(ns * 4 + ss) * 2) * 3 * DD;
+        const float* Hrec = Yrec + 3 * DD;
+        const float* Hfin = recd + ((size_t)(nf * 4 + sf) * 2 + 1) * 3 * DD;
         // external field at the finishing and at the starting stage
         const Field3 hF = hext_at(pr, pr.tau0 + ((double)nf + stage_frac(4, sf)) * pr.dtau_d);
         const Field3 hS = hext_at(pr, pr.tau0 + ((double)ns + stage_frac(4, ss)) * pr.dtau_d);
         const float hh[3] = {(float)hF.x, (float)hF.y, (float)hF.z};
         const float hsx = (float)hS.x, hsy = (float)hS.y, hsz = (float)hS.z;
-        for (int idx = tid<OPQ>(); idx < U * D; idx += NT) {
-            const int uu = idx / D, i = idx - uu * D;
+        const unsigned fb = fin ? st_bytes : 0u, sb = sta ? st_bytes : 0u;   // unused sources read as zeros
+        const CellSrc src{make_rsrc(d.aux, fb), make_rsrc(d.acc, fb), make_rsrc(Hfin, fb), make_rsrc(Hrec, sb),
+                          make_rsrc(m, sb)};
+        {
+            float hB[IH], hY[IH];
+            SRow sv[IS];
+            if (fin) halo_load_t(BoolC<false>{}, b, Bf, hB);   // zero outside the disk already
+            if (sta) halo_load_t(BoolC<true>{}, b, Yrec, hY);
+            if (fin) row_load(b, sv);
+            if (sta) record_stencil(hY);
+            if (fin) halo_store(hB);
+            if constexpr (EARLY) cell_loads(b, src);
+            if (fin)
+                row_unpack_inverse(sv);
+            else
+                __syncthreads();
+        }
+#pragma unroll
+        for (int q = 0; q < IC; ++q) {
+            int uu, i;
+            if (!cell_item(tid<OPQ>() + q * NT, uu, i)) continue;
             const int p = b * U + uu;
             if (p >= d.n_pairs) continue;
             const int j0 = 2 * p;
-            float bc[4][3], bl[2][3], br[2][3], yc[4][3], yl[2][3], yr[2][3];
-            float ax[2][3], ac[2][3], hf[2][3], hs[2][3], yb0[2][3];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = j0 - 1 + r;
-                const bool ok = j >= 0 && j < D && in_disk(j, i, D);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    bc[r][c] = (fin && ok) ? ld_sh(Bf + c * DD + j * D + i) : 0.f;
-                    yc[r][c] = (sta && ok) ? Yrec[c * DD + j * D + i] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int j = j0 + r;
-                const bool okl = j < D && i > 0 && in_disk(j, i - 1, D);
-                const bool okr = j < D && i + 1 < D && in_disk(j, i + 1, D);
-                const bool okc = j < D && in_disk(j, i, D);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const int cell = c * DD + j * D + i;
-                    bl[r][c] = (fin && okl) ? ld_sh(Bf + cell - 1) : 0.f;
-                    br[r][c] = (fin && okr) ? ld_sh(Bf + cell + 1) : 0.f;
-                    yl[r][c] = (sta && okl) ? Yrec[cell - 1] : 0.f;
-                    yr[r][c] = (sta && okr) ? Yrec[cell + 1] : 0.f;
-                    ax[r][c] = (fin && okc) ? d.aux[cell] : 0.f;
-                    ac[r][c] = (fin && okc) ? gbl(d.acc)[cell] : 0.f;
-                    hf[r][c] = (fin && okc) ? Hfin[cell] : 0.f;
-                    hs[r][c] = (sta && okc) ? Hrec[cell] : 0.f;
-                    yb0[r][c] = (sta && okc) ? ld_sh(m + cell) : 0.f;
-                }
-            }
+            const VGath& V = vg[q];
             const float2 hz2 = BUF(2, uu)[padb(i)];
             float nxt[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
 #pragma unroll
@@ -890,6 +957,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                 const int j = j0 + r;
                 if (j >= D) break;
                 const int cell = j * D + i;
+                if constexpr (!EARLY) cell_load(b, q, r, src);
                 if (!in_disk(j, i, D)) {
                     if (sta) {
                         st_sh(Bs + cell, 0.f);
@@ -899,19 +967,18 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                     continue;
                 }
                 float yprev[3] = {0.f, 0.f, 0.f};
-                float ybar[3] = {yb0[r][0], yb0[r][1], yb0[r][2]};
+                float ybar[3] = {V.y[r][0], V.y[r][1], V.y[r][2]};
                 if (fin) {
                     const float2 kxy = BUF(r, uu)[padb(i)];
                     const float Kb[3] = {kxy.x, kxy.y, r == 0 ? hz2.x : hz2.y};
                     float accn[3];
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
-                        const float ex = bc[r][c] + bc[r + 2][c] + bl[r][c] + br[r][c];
-                        yprev[c] = ax[r][c] + ex + cf * Kb[c];
-                        accn[c] = ac[r][c] + yprev[c];
+                        const Sten B = stencil(c, uu, i);
+                        yprev[c] = V.ax[r][c] + B.sum(r) + cf * Kb[c];
+                        accn[c] = V.ac[r][c] + yprev[c];
+                        e_dm += (double)B.col[r + 1] * ((double)hh[c] + (double)V.hf[r][c]);
                     }
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) e_dm += (double)bc[r + 1][c] * ((double)hh[c] + (double)hf[r][c]);
                     if (sf == 0) {  // step nf complete: yb_nf = accumulated cotangent
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
@@ -933,10 +1000,10 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                     const float kx = w * ybar[0] + v * yprev[0];
                     const float ky = w * ybar[1] + v * yprev[1];
                     const float kz = w * ybar[2] + v * yprev[2];
-                    const float Yx = yc[r + 1][0], Yy = yc[r + 1][1], Yz = yc[r + 1][2];
-                    const float bx = (yc[r][0] + yc[r + 2][0] + yl[r][0] + yr[r][0]) + cf * (hsx + hs[r][0]);
-                    const float by = (yc[r][1] + yc[r + 2][1] + yl[r][1] + yr[r][1]) + cf * (hsy + hs[r][1]);
-                    const float bz = (yc[r][2] + yc[r + 2][2] + yl[r][2] + yr[r][2]) + cf * (hsz + hs[r][2]);
+                    const float Yx = V.Y[r][0], Yy = V.Y[r][1], Yz = V.Y[r][2];
+                    const float bx = V.Yx[r][0] + cf * (hsx + V.hs[r][0]);
+                    const float by = V.Yx[r][1] + cf * (hsy + V.hs[r][1]);
+                    const float bz = V.Yx[r][2] + cf * (hsz + V.hs[r][2]);
                     // Y x b
                     const float px = Yy * bz - Yz * by, py = Yz * bx - Yx * bz, pz = Yx * by - Yy * bx;
                     // kb x Y
@@ -1143,34 +1210,17 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     // Thread sums (float64): q[0] = max residual |m x (b + b^lam)| of cur, q[1..2] = C(cur),
     // q[3..4] = C(nxt), q[5..7] = Jacobian entries (xx, xy, yy) of C(nxt) in lam.
     double rq[8];
-    auto relax_update = [&](int b, const float* cur, float* nxt, double lx, double ly, double Xc, double Yc) {
+    auto relax_update = [&](int b, float* nxt, double lx, double ly, double Xc, double Yc) {
         const double half = (D - 1) / 2.0;
         const float kap = (float)a.kappa;
-        for (int idx = tid<OPQ>(); idx < U * D; idx += NT) {
-            const int uu = idx / D, i = idx - uu * D;
+#pragma unroll
+        for (int q = 0; q < IC; ++q) {
+            int uu, i;
+            if (!cell_item(tid<OPQ>() + q * NT, uu, i)) continue;
             const int p = b * U + uu;
             if (p >= d.n_pairs) continue;
             const int j0 = 2 * p;
-            float col[4][3], lft[2][3], rgt[2][3];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = j0 - 1 + r;
-                const bool ok = j >= 0 && j < D && in_disk(j, i, D);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) col[r][c] = ok ? ld_sh(cur + c * DD + j * D + i) : 0.f;
-            }
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int j = j0 + r;
-                const bool okl = j < D && i > 0 && in_disk(j, i - 1, D);
-                const bool okr = j < D && i + 1 < D && in_disk(j, i + 1, D);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const int cell = c * DD + j * D + i;
-                    lft[r][c] = okl ? ld_sh(cur + cell - 1) : 0.f;
-                    rgt[r][c] = okr ? ld_sh(cur + cell + 1) : 0.f;
-                }
-            }
+            const Sten sx = stencil(0, uu, i), sy = stencil(1, uu, i), sz = stencil(2, uu, i);
             const float2 hz2 = BUF(2, uu)[padb(i)];
             float nxt_v[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
 #pragma unroll
@@ -1181,13 +1231,13 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                 if (in_disk(j, i, D)) {
                     const float2 hxy = BUF(r, uu)[padb(i)];
                     const float Hz = r == 0 ? hz2.x : hz2.y;
-                    const float mx = col[r + 1][0], my = col[r + 1][1], mz = col[r + 1][2];
+                    const float mx = sx.col[r + 1], my = sy.col[r + 1], mz = sz.col[r + 1];
                     double dx = ((double)i - half) - Xc, dy = ((double)j - half) - Yc;
                     if (a.relax_cut2 > 0.0 && !(dx * dx + dy * dy < a.relax_cut2)) dx = dy = 0.0;
                     const float bl = (float)(2.0 * (double)mz * (lx * dx + ly * dy));
-                    const float bx = (col[r][0] + col[r + 2][0] + lft[r][0] + rgt[r][0]) + cf * (hxf + hxy.x);
-                    const float by = (col[r][1] + col[r + 2][1] + lft[r][1] + rgt[r][1]) + cf * (hyf + hxy.y);
-                    const float bz = (col[r][2] + col[r + 2][2] + lft[r][2] + rgt[r][2]) + cf * (hzf + Hz) + bl;
+                    const float bx = sx.sum(r) + cf * (hxf + hxy.x);
+                    const float by = sy.sum(r) + cf * (hyf + hxy.y);
+                    const float bz = sz.sum(r) + cf * (hzf + Hz) + bl;
                     const float px = my * bz - mz * by, py = mz * bx - mx * bz, pz = mx * by - my * bx;
                     rq[0] = fmax(rq[0], (double)sqrtf(px * px + py * py + pz * pz));
                     const double w0 = (double)mz * (double)mz;
@@ -1253,10 +1303,20 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             column_pass();
             if (!group_barrier(d.bar, d.bar_lines, ++epoch, g, G, a.err, a.spin_limit)) return;
             for (int q = 0; q < 8; ++q) rq[q] = 0.0;
-            for (int b = g; b < n_rb; b += G) {
-                row_inverse(b);
-                relax_update(b, cur, nxt, lx, ly, Xc, Yc);
-                row_forward_store(b);
+            // the next iteration's staged rows and spectra are in flight during this one's transforms
+            if (g < n_rb) {
+                float hv[IH];
+                SRow sv[IS];
+                halo_load(g, cur, hv, sweep == 0);   // only the caller's state needs the disk test
+                row_load(g, sv);
+                for (int b = g; b < n_rb; b += G) {
+                    halo_store(hv);
+                    row_unpack_inverse(sv);
+                    relax_update(b, nxt, lx, ly, Xc, Yc);
+                    halo_load(b + G, cur, hv, sweep == 0);
+                    row_load(b + G, sv);
+                    row_forward_store(b);
+                }
             }
             // workgroup partials: max for the residual, sums for the rest
             {
@@ -1277,13 +1337,27 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
                 }
             }
             if (!group_barrier(d.bar, d.bar_lines, ++epoch, g, G, a.err, a.spin_limit)) return;
-            // every workgroup of the disk reduces the same partials in the same order
-            double t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int gg = 0; gg < G; ++gg)
-                for (int q = 0; q < 8; ++q) {
-                    const double v = ld_shd(d.part + gg * PART_STRIDE + q);
-                    t[q] = (q == 0) ? fmax(t[q], v) : t[q] + v;
-                }
+            // every wavefront of the disk reduces the same partials in the same order: lane
+            // (h, q) takes value q of the workgroups h, h + 8, ... with 64 workgroups' loads in
+            // flight (one thread after the other took 35 of the 46 us of a sweep on 129)
+            const __amdgpu_buffer_rsrc_t Pr = make_rsrc(d.part, (unsigned)(G * PART_STRIDE) * 8u);
+            double acc = 0.0;
+            for (int g0 = lane >> 3; g0 < G; g0 += 64) {
+                double v[8];
+#pragma unroll
+                for (int h = 0; h < 8; ++h)
+                    v[h] = __builtin_bit_cast(double, bld2(Pr, ((g0 + 8 * h) * PART_STRIDE + (lane & 7)) * 8));
+#pragma unroll
+                for (int h = 0; h < 8; ++h) acc = (lane & 7) == 0 ? fmax(acc, v[h]) : acc + v[h];   // past G: zeros
+            }
+            double t[8];
+#pragma unroll
+            for (int o = 8; o < 64; o <<= 1) {
+                const double v = __shfl_xor(acc, o, 64);
+                acc = (lane & 7) == 0 ? fmax(acc, v) : acc + v;
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t[q] = __shfl(acc, q, 64);
             res = t[0];
             Cx = t[1];
             Cy = t[2];
@@ -1328,11 +1402,12 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
         const long long K = NST * a.nsteps;
         for (long long k = 0; k <= K; ++k) {
             for (int b = g; b < n_rb; b += G) {
-                if (k > 0) row_inverse(b);
-                if constexpr (MODE == MODE_RK4_VJP)
+                if constexpr (MODE == MODE_RK4_VJP) {
                     vjp_update(b, k, K);
-                else
+                } else {
+                    if (k > 0) row_inverse(b);
                     heun_vjp_update(b, k, K);
+                }
                 if (k < K) row_forward_store(b);
             }
             if (k == K) break;
@@ -1473,9 +1548,12 @@ constexpr int halo_floats(int PMAX) {
     return n;
 }
 
-// The integrators keep three wavefronts per SIMD resident (the register
-// budget the compiler must meet); the other modes take what they need.
-constexpr int min_waves_per_simd(int mode) { return (mode == MODE_RK4 || mode == MODE_HEUN) ? 3 : 1; }
+// The integrators and the relaxation keep three wavefronts per SIMD resident (the
+// register budget the compiler must meet; a plan tuned for an integrator then
+// holds the relaxation too); the other modes take what they need.
+constexpr int min_waves_per_simd(int mode) {
+    return mode == MODE_RK4 || mode == MODE_HEUN || mode == MODE_RELAX ? 3 : 1;
+}
 
 template <int UG, int POL, int MODE, int PMAX, bool SER>
 __global__ __launch_bounds__(WG_THREADS* UG) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(MODE))))
