@@ -327,10 +327,23 @@ int choose_P(int D, int P_override, int* P) {
 // Units (transforms per component) a workgroup carries at once, for FFT size P.
 int units_per_wg(int P, int UG, int RSEL) { return UG * (64 / (P / radix_for(P, RSEL))); }
 
-int default_unit_groups(llg_disk) {
-    // narrow workgroups spread a disk over the most CUs; measured best for a
-    // lone D=100 disk (one transform per workgroup and phase) and for batches
-    return 1;
+// Unit groups of the default plan.  Two where the disks are large (P >= 256) and few
+// enough to get a workgroup per column tile pair on every CU: half the arrivals at
+// each barrier (lone R = 100 nm disk 43.4 -> 36.5 us per RK4 step, lone R = 250 nm
+// 73.3 -> 64.1, four of them 104 -> 84); one otherwise, for the most CUs per disk
+// and workgroups that share a CU evenly.
+int default_unit_groups(llg_disk h) {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 1;
+    long long tiles = 0;
+    for (int P : h->P) {
+        if (P < 256) return 1;
+        const int U = units_per_wg(P, 2, 0);
+        tiles += (P / 2 + 1 + U - 1) / U;
+    }
+    return tiles <= 2 * ncu + ncu / 4 ? 2 : 1;
 }
 
 // Workgroups per disk and the workgroup-to-disk map of the persistent launch.
@@ -356,9 +369,11 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         oc[k] = h->onchip_pmax > 0 && h->P[k] <= h->onchip_pmax;
         if (oc[k]) oc_lds = std::max(oc_lds, (unsigned)(3 * (h->P[k] / 2 + 1) * h->desc[k].Dp * sizeof(float2)));
     }
-    int cap = 0;
+    int cap = 0, dev = 0, ncu = 0;
     int rc = max_coresident_workgroups(UG, RSEL, h->PMAX, &cap, modes, oc_lds);
     if (rc) return rc;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     if (cap <= 0)
         return fail(LLG_EUNSUPPORTED, "no workgroup of " + std::to_string(WG_THREADS * UG) + " threads fits a CU with " +
                                           std::to_string(oc_lds) + " bytes of on-chip spectra");
@@ -393,7 +408,11 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         }
     } else {
         if (!(scale > 0.0 && scale <= 1.0)) return fail(LLG_EINVAL, "plan scale must be in (0, 1]");
-        const long long budget = std::max<long long>(n, (long long)std::floor(cap * scale));
+        // (the library's own plan keeps one workgroup of several groups per CU: CUs that carry two next to
+        // CUs that carry one hold their disks up; 16 disks of R = 40 nm with two unit groups: 43.5 us per RK4
+        // step on 144 workgroups, 68.9 on 272)
+        const int room = modes == ALL_MODES && UG > 1 ? std::min(cap, ncu) : cap;
+        const long long budget = std::max<long long>(n, (long long)std::floor(room * scale));
         double lo = 0.0, hi = 0.0;
         for (int k = 0; k < n; ++k) hi = std::max(hi, stage_time(k, 1));
         auto total = [&](double T) {
