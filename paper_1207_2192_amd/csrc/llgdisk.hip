@@ -179,7 +179,7 @@ struct llg_disk_s {
     bool timing = false;
     int* wg2disk = nullptr;
     int* wg2local = nullptr;
-    int n_wg = 0;
+    int n_wg = 0, rounds = 1;         // workgroups of a launch, launches of a call (plan)
     unsigned int* bars = nullptr;
     int n_bars = 0;                   // words of the current plan's counters
     int* err_dev = nullptr;
@@ -357,7 +357,16 @@ int default_unit_groups(llg_disk h) {
 // single-transform P = 256 column iteration); the smallest target T whose
 // per-disk counts (the fewest workgroups that meet T) fit the budget is found
 // by bisection.  Disks on chip (P <= h->onchip_pmax) take one workgroup each.
-int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = ALL_MODES, double scale = 1.0) {
+//
+// With two rounds the call steps one half of the disks to its end before the
+// other, in a launch each on all workgroups: half as many disks share an XCD's L2, and
+// the row spectra that its workgroups exchange are more often still there (64
+// replicas of R = 250 nm, 1.6 MB of spectra each: 286 us per Heun step on 4
+// workgroups each, 265 in two rounds on 8; four rounds on 16 lose more to
+// uneven tiles than they gain).  Small disks do not gain: the ragged ensemble takes
+// 357 us in one round, 400 in two.
+int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = ALL_MODES, double scale = 1.0,
+         int rounds = 1) {
     if (UG != 1 && UG != 2 && UG != 4) return fail(LLG_EINVAL, "unit groups must be 1, 2 or 4");
     if (RSEL < 0 || RSEL > 3) return fail(LLG_EINVAL, "transform policy must be 0, 1, 2 or 3");
     const int n = h->n;
@@ -401,54 +410,25 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         while (g < useful[k] && stage_time(k, g) > T) ++g;
         return g;
     };
-    if (wg_per_disk) {
-        for (int k = 0; k < n; ++k) {
-            if (wg_per_disk[k] < 1) return fail(LLG_EINVAL, "wg_per_disk must be >= 1");
-            G[k] = oc[k] ? 1 : std::min(wg_per_disk[k], useful[k]);
-        }
-    } else {
-        if (!(scale > 0.0 && scale <= 1.0)) return fail(LLG_EINVAL, "plan scale must be in (0, 1]");
-        // (the library's own plan keeps one workgroup of several groups per CU: CUs that carry two next to
-        // CUs that carry one hold their disks up; 16 disks of R = 40 nm with two unit groups: 43.5 us per RK4
-        // step on 144 workgroups, 68.9 on 272)
-        const int room = modes == ALL_MODES && UG > 1 ? std::min(cap, ncu) : cap;
-        const long long budget = std::max<long long>(n, (long long)std::floor(room * scale));
-        double lo = 0.0, hi = 0.0;
-        for (int k = 0; k < n; ++k) hi = std::max(hi, stage_time(k, 1));
-        auto total = [&](double T) {
-            long long t = 0;
-            for (int k = 0; k < n; ++k) t += g_for(k, T);
-            return t;
-        };
-        for (int it = 0; it < 60; ++it) {   // smallest T whose counts fit the budget
-            const double mid = 0.5 * (lo + hi);
-            if (total(mid) <= budget)
-                hi = mid;
-            else
-                lo = mid;
-        }
-        for (int k = 0; k < n; ++k) G[k] = g_for(k, hi);
-    }
-    long long total = std::accumulate(G.begin(), G.end(), 0LL);
-    while (total > cap) {  // trim the disks with the most workgroups
-        int kmax = (int)(std::max_element(G.begin(), G.end()) - G.begin());
-        if (G[kmax] <= 1) break;
-        --G[kmax];
-        --total;
-    }
-    if (total > cap)
-        return fail(LLG_EUNSUPPORTED, "batch needs " + std::to_string(total) + " workgroups but only " +
-                                          std::to_string(cap) + " can be co-resident");
-
-    // Disks whose workgroups all fit one XCD stay on one XCD (workgroup w runs
-    // on XCD w mod 8); larger disks take consecutive ids and span the XCDs.
-    std::vector<int> w2d, w2l;
+    // the disks of each round, large and small dealt alike
+    std::vector<std::vector<int>> sets(rounds);
     {
-        std::vector<std::vector<std::pair<int, int>>> lanes(NXCD);
-        std::vector<long long> load(NXCD, 0);
-        std::vector<int> big;
         std::vector<int> order(n);
         std::iota(order.begin(), order.end(), 0);
+        if (rounds > 1) std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
+        for (int i = 0; i < n; ++i) sets[i % rounds].push_back(order[i]);
+    }
+    // Workgroup map of one round.  Disks whose workgroups all fit one XCD stay on
+    // one XCD (workgroup w runs on XCD w mod 8); larger disks take consecutive ids
+    // and span the XCDs.
+    auto layout = [&](const std::vector<int>& ids, std::vector<int>& w2d, std::vector<int>& w2l) {
+        auto add = [&](int k, int l) {
+            w2d.push_back(k);
+            w2l.push_back(l);
+        };
+        std::vector<std::vector<std::pair<int, int>>> lanes(NXCD);
+        std::vector<long long> load(NXCD, 0);
+        std::vector<int> order(ids), big;
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return G[x] > G[y]; });
         for (int k : order) {
             if (n > 1 && G[k] * NXCD <= cap) {
@@ -460,39 +440,83 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
             }
         }
         for (int k : big)
-            for (int l = 0; l < G[k]; ++l) {
-                w2d.push_back(k);
-                w2l.push_back(l);
-            }
-        while (w2d.size() % NXCD) {
-            w2d.push_back(-1);
-            w2l.push_back(0);
-        }
+            for (int l = 0; l < G[k]; ++l) add(k, l);
+        while (w2d.size() % NXCD) add(-1, 0);
         size_t depth = 0;
         for (auto& l : lanes) depth = std::max(depth, l.size());
         for (size_t s = 0; s < depth; ++s)
             for (int x = 0; x < NXCD; ++x) {
-                if (s < lanes[x].size()) {
-                    w2d.push_back(lanes[x][s].first);
-                    w2l.push_back(lanes[x][s].second);
-                } else {
-                    w2d.push_back(-1);
-                    w2l.push_back(0);
-                }
+                if (s < lanes[x].size())
+                    add(lanes[x][s].first, lanes[x][s].second);
+                else
+                    add(-1, 0);
             }
         while (!w2d.empty() && w2d.back() < 0) {
             w2d.pop_back();
             w2l.pop_back();
         }
-    }
-    if ((int)w2d.size() > cap) {  // the XCD-aligned layout does not fit: consecutive ids
-        w2d.clear();
-        w2l.clear();
-        for (int k = 0; k < n; ++k)
-            for (int l = 0; l < G[k]; ++l) {
-                w2d.push_back(k);
-                w2l.push_back(l);
+        if ((int)w2d.size() > cap) {  // the XCD-aligned layout does not fit: consecutive ids
+            w2d.clear();
+            w2l.clear();
+            for (int k : ids)
+                for (int l = 0; l < G[k]; ++l) add(k, l);
+        }
+    };
+    if (wg_per_disk) {
+        for (int k = 0; k < n; ++k) {
+            if (wg_per_disk[k] < 1) return fail(LLG_EINVAL, "wg_per_disk must be >= 1");
+            G[k] = oc[k] ? 1 : std::min(wg_per_disk[k], useful[k]);
+        }
+    } else {
+        if (!(scale > 0.0 && scale <= 1.0)) return fail(LLG_EINVAL, "plan scale must be in (0, 1]");
+        // (the library's own plan keeps one workgroup of several groups per CU: CUs that carry two next to
+        // CUs that carry one hold their disks up; 16 disks of R = 40 nm with two unit groups: 43.5 us per RK4
+        // step on 144 workgroups, 68.9 on 272)
+        const int room = modes == ALL_MODES && UG > 1 ? std::min(cap, ncu) : cap;
+        const long long budget = std::max<long long>(sets[0].size(), (long long)std::floor(room * scale));
+        for (const std::vector<int>& ids : sets) {
+            double lo = 0.0, hi = 0.0;
+            for (int k : ids) hi = std::max(hi, stage_time(k, 1));
+            auto total = [&](double T) {
+                long long t = 0;
+                for (int k : ids) t += g_for(k, T);
+                return t;
+            };
+            for (int it = 0; it < 60; ++it) {   // smallest T whose counts fit the budget
+                const double mid = 0.5 * (lo + hi);
+                if (total(mid) <= budget)
+                    hi = mid;
+                else
+                    lo = mid;
             }
+            for (int k : ids) G[k] = g_for(k, hi);
+        }
+    }
+    std::vector<int> w2d, w2l;
+    size_t n_wg = 0;
+    std::vector<std::vector<int>> sd, sl;   // the maps of each round
+    for (const std::vector<int>& ids : sets) {
+        long long total = 0;
+        for (int k : ids) total += G[k];
+        while (total > cap) {  // trim the disks with the most workgroups
+            const int kmax = *std::max_element(ids.begin(), ids.end(), [&](int x, int y) { return G[x] < G[y]; });
+            if (G[kmax] <= 1) break;
+            --G[kmax];
+            --total;
+        }
+        if (total > cap)
+            return fail(LLG_EUNSUPPORTED, "batch needs " + std::to_string(total) + " workgroups but only " +
+                                              std::to_string(cap) + " can be co-resident");
+        sd.emplace_back();
+        sl.emplace_back();
+        layout(ids, sd.back(), sl.back());
+        n_wg = std::max(n_wg, sd.back().size());
+    }
+    for (size_t r = 0; r < sets.size(); ++r) {
+        sd[r].resize(n_wg, -1);
+        sl[r].resize(n_wg, 0);
+        w2d.insert(w2d.end(), sd[r].begin(), sd[r].end());
+        w2l.insert(w2l.end(), sl[r].begin(), sl[r].end());
     }
     h->dfree(h->wg2disk);
     h->dfree(h->wg2local);
@@ -501,7 +525,8 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
     if ((rc = h->dalloc(&h->wg2local, w2l.size()))) return rc;
     HIP_TRY(hipMemcpy(h->wg2disk, w2d.data(), w2d.size() * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(h->wg2local, w2l.data(), w2l.size() * sizeof(int), hipMemcpyHostToDevice));
-    h->n_wg = (int)w2d.size();
+    h->n_wg = (int)n_wg;
+    h->rounds = (int)sets.size();
     h->n_bars = 0;
     for (int k = 0; k < n; ++k) {
         DiskDesc& d = h->desc[k];
@@ -840,8 +865,12 @@ int launch(llg_disk h, int mode, float* m, float* out, long long nsteps, unsigne
         HIP_TRY(hipGetLastError());
         if (desc_override) a.disks = desc_override;
         if (h->timing) HIP_TRY(hipEventRecord(h->time_ev[mode][0], st));
-        HIP_TRY(hipLaunchCooperativeKernel(persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, series != nullptr),
-                                           dim3(h->n_wg), dim3(WG_THREADS * h->UG), args, dyn, st));
+        for (int r = 0; r < h->rounds; ++r) {
+            a.wg2disk = h->wg2disk + (size_t)r * h->n_wg;
+            a.wg2local = h->wg2local + (size_t)r * h->n_wg;
+            HIP_TRY(hipLaunchCooperativeKernel(persistent_kernel(mode, h->UG, h->RSEL, h->PMAX, series != nullptr),
+                                               dim3(h->n_wg), dim3(WG_THREADS * h->UG), args, dyn, st));
+        }
     }
     if (h->timing) {
         HIP_TRY(hipEventRecord(h->time_ev[mode][1], st));
@@ -1116,7 +1145,7 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     std::vector<int> ocs = {0};
     if (pmin <= 64) ocs.push_back(64);
     if (pmin <= 128 && std::count_if(h->P.begin(), h->P.end(), [](int P) { return P == 128; }) > 0) ocs.push_back(128);
-    struct Cand { int UG, RSEL; double scale; int oc; bool resident; };
+    struct Cand { int UG, RSEL; double scale; int oc; bool resident; int rounds = 1; };
     std::vector<Cand> cands;
     for (int ug : {1, 2, 4})
         for (int rs : {0, 1, 2, 3})
@@ -1124,13 +1153,15 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     for (size_t q = 1; q < ocs.size(); ++q)   // on chip: one unit group, the full workgroup budget
         for (int rs : {0, 1, 2, 3}) cands.push_back({1, rs, 1.0, ocs[q], false});
     if (can_be_resident(h)) cands.push_back({1, 0, 1.0, 0, true});
+    if (h->n >= 2 * NXCD && h->PMAX >= 512)   // two rounds, where the spectra are large
+        for (int ug : {1, 4}) cands.push_back({ug, 3, 1.0, 0, false, 2});
     double best = 1e300;
     Cand bestc{h->UG, h->RSEL, 1.0, h->onchip_pmax, h->resident};
     for (const Cand& c : cands) {
         const unsigned modes = c.resident ? ALL_MODES : 1u << mode;   // the plan keeps the integrator co-resident
         h->onchip_pmax = c.oc;
         h->resident = c.resident;
-        if ((rc = plan(h, c.UG, c.RSEL, nullptr, modes, c.scale))) continue;
+        if ((rc = plan(h, c.UG, c.RSEL, nullptr, modes, c.scale, c.rounds))) continue;
         float ms = 0.f;
         bool ok = true;
         for (int rep = 0; rep < 2 && ok; ++rep) {
@@ -1155,7 +1186,7 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     h->onchip_pmax = bestc.oc;
     h->resident = bestc.resident;
     const unsigned modes = bestc.resident ? ALL_MODES : 1u << mode;
-    if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, modes, bestc.scale))) return rc;
+    if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, modes, bestc.scale, bestc.rounds))) return rc;
     if (best_us) *best_us = best * 1e3 / (double)probe_steps;
     return 0;
 }
@@ -1395,10 +1426,11 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
     // ... and of the current launch plan
     int *gw2d = nullptr, *gw2l = nullptr;
     DiskDesc* gdesc = nullptr;
-    HIP_TRY(g->dalloc(&gw2d, h->n_wg));
-    HIP_TRY(g->dalloc(&gw2l, h->n_wg));
-    HIP_TRY(hipMemcpy(gw2d, h->wg2disk, h->n_wg * sizeof(int), hipMemcpyDeviceToDevice));
-    HIP_TRY(hipMemcpy(gw2l, h->wg2local, h->n_wg * sizeof(int), hipMemcpyDeviceToDevice));
+    const size_t map = (size_t)h->n_wg * h->rounds;
+    HIP_TRY(g->dalloc(&gw2d, map));
+    HIP_TRY(g->dalloc(&gw2l, map));
+    HIP_TRY(hipMemcpy(gw2d, h->wg2disk, map * sizeof(int), hipMemcpyDeviceToDevice));
+    HIP_TRY(hipMemcpy(gw2l, h->wg2local, map * sizeof(int), hipMemcpyDeviceToDevice));
     std::vector<DiskDesc> desc = h->desc;
     for (DiskDesc& d : desc) HIP_TRY(g->dalloc(&d.part, (size_t)PART_STRIDE * d.G));
     HIP_TRY(g->dalloc(&gdesc, h->n));
@@ -1436,10 +1468,14 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
         kp.sharedMemBytes = 0;
         HIP_TRY(hipGraphAddKernelNode(&np, g->graph, nullptr, 0, &kp));
     } else {
-        HIP_TRY(hipGraphAddKernelNode(&np, g->graph, &nz, 1, &kp));
         hipKernelNodeAttrValue coop{};
         coop.cooperative = 1;
-        HIP_TRY(hipGraphKernelNodeSetAttribute(np, hipKernelNodeAttributeCooperative, &coop));
+        for (int r = 0; r < h->rounds; ++r) {   // the rounds of the plan, one after the other
+            a.wg2disk = gw2d + (size_t)r * h->n_wg;
+            a.wg2local = gw2l + (size_t)r * h->n_wg;
+            HIP_TRY(hipGraphAddKernelNode(&np, g->graph, r == 0 ? &nz : &np, 1, &kp));
+            HIP_TRY(hipGraphKernelNodeSetAttribute(np, hipKernelNodeAttributeCooperative, &coop));
+        }
     }
     // node 3 (Heun): advance the step counter so that the next replay continues the noise stream
     if (integrator == 1) {
