@@ -5,8 +5,11 @@ integrates n_seg * seg_steps RK4 steps (noise = None) or Heun steps (noise =
 (seed, step0, replica); segment s uses the step indices step0 + s*seg_steps ...)
 on the GPU and returns the vortex core position r_c (nm, float64) at the
 n_seg + 1 checkpoints t = 0, seg_steps, ...  Checkpoints of the state are kept
-every seg_steps steps.  The backward pass recomputes each segment once with the
-stage record (llg_rk4_record / llg_heun_record) and runs the reverse sweep
+every seg_steps steps.  Where a gradient is asked for, the forward pass steps with
+the stage record (llg_rk4_record / llg_heun_record) and keeps it for as many
+segments as RECORD_SHARE of the device's memory holds (5000 RK4 steps at R = 80 nm:
+3 GB of 288); the backward pass recomputes the record of the others from their
+checkpoints.  It runs the reverse sweep
 (llg_rk4_vjp / llg_heun_vjp, the noise replayed from its counter); the
 cotangent of each sampled core position enters through llg_core_position_vjp.
 Gradients come out for m0, alpha and c = a^2/lambda_ex^2;
@@ -22,6 +25,33 @@ import torch
 from .api import Disk, LLGParams
 
 
+# Records are kept between the passes up to this share of the device's memory (18 GB
+# of 288) and half of what is free.  A recorded RK4 step costs 36.3 us against 35.7
+# plain at R = 80 nm (17.1 against 16.3 at 30 nm), so recomputing a segment is a
+# whole forward pass over: 2 x 50 steps at R = 80 nm, forward and backward, 13.5 ms
+# recomputed and 10.2 ms kept.
+RECORD_SHARE = 1.0 / 16
+
+
+def _kept_segments(n_seg: int, seg_floats: int, device) -> int:
+    """Segments whose record the forward pass may keep until the backward pass."""
+    free, total = torch.cuda.mem_get_info(device)
+    return max(0, min(n_seg, int(min(RECORD_SHARE * total, 0.5 * free) // (4 * max(seg_floats, 1)))))
+
+
+def _record_floats(disk: Disk, seg_steps: int, noise) -> int:
+    return (8 if noise is None else 4) * seg_steps * disk.state_size
+
+
+def _record(disk: Disk, m, seg_steps: int, prm, noise, s: int, rec):
+    """Segment s of the trajectory in place, with its stage record."""
+    if noise is None:
+        disk.rk4_record(m, seg_steps, prm, rec)
+    else:
+        seed, step0, rep = noise
+        disk.heun_record(m, seg_steps, prm, rec, seed=seed, step0=step0 + s * seg_steps, replica=rep)
+
+
 class CoreTrajectory(torch.autograd.Function):
     @staticmethod
     def forward(ctx, m0, alpha, c, disk: Disk, params: LLGParams, n_seg: int, seg_steps: int,
@@ -34,15 +64,21 @@ class CoreTrajectory(torch.autograd.Function):
         m = m0.detach().clone().contiguous()
         ckpts = [m.clone()]
         cores = [disk.vortex_core_position(m, lambda_ex_nm)]
+        recs = [None] * n_seg
+        floats = _record_floats(disk, seg_steps, noise)
+        keep = _kept_segments(n_seg, floats, m.device) if any(ctx.needs_input_grad) and seg_steps > 0 else 0
         for s in range(n_seg):
-            if noise is None:
+            if s >= n_seg - keep:
+                recs[s] = torch.empty(floats, dtype=torch.float32, device=m.device)
+                _record(disk, m, seg_steps, prm, noise, s, recs[s])
+            elif noise is None:
                 disk.rk4_step(m, seg_steps, prm)
             else:
                 seed, step0, rep = noise
                 disk.heun_step(m, seg_steps, prm, seed=seed, step0=step0 + s * seg_steps, replica=rep)
             ckpts.append(m.clone())
             cores.append(disk.vortex_core_position(m, lambda_ex_nm))
-        ctx.noise = noise
+        ctx.noise, ctx.recs = noise, recs
         ctx.disk, ctx.prm, ctx.n_seg, ctx.seg = disk, prm, n_seg, seg_steps
         ctx.lam, ctx.ckpts, ctx.cores = lambda_ex_nm, ckpts, cores
         ctx.alpha_like, ctx.c_like = alpha, c
@@ -54,19 +90,20 @@ class CoreTrajectory(torch.autograd.Function):
         grad_rc = grad_rc.to(torch.float64).contiguous()
         ybar = torch.zeros_like(ctx.ckpts[0])
         pgrad = torch.zeros(2, dtype=torch.float64, device=ybar.device)
-        per_step = 8 if ctx.noise is None else 4
-        rec = torch.empty(per_step * seg * disk.state_size, dtype=torch.float32, device=ybar.device)
+        rec = None
         disk.core_position_vjp(ctx.ckpts[-1], ctx.lam, ctx.cores[-1], grad_rc[-1], ybar)
         for s in reversed(range(ctx.n_seg)):
-            m = ctx.ckpts[s].clone()
+            cur, ctx.recs[s] = ctx.recs[s], None          # given back once read; a second backward pass recomputes it
+            if cur is None:
+                if rec is None:
+                    rec = torch.empty(_record_floats(disk, seg, ctx.noise), dtype=torch.float32, device=ybar.device)
+                cur = rec
+                _record(disk, ctx.ckpts[s].clone(), seg, prm, ctx.noise, s, cur)
             if ctx.noise is None:
-                disk.rk4_record(m, seg, prm, rec)
-                disk.rk4_vjp(rec, seg, ybar, pgrad, prm)
+                disk.rk4_vjp(cur, seg, ybar, pgrad, prm)
             else:
                 seed, step0, rep = ctx.noise
-                kw = dict(seed=seed, step0=step0 + s * seg, replica=rep)
-                disk.heun_record(m, seg, prm, rec, **kw)
-                disk.heun_vjp(rec, seg, ybar, pgrad, prm, **kw)
+                disk.heun_vjp(cur, seg, ybar, pgrad, prm, seed=seed, step0=step0 + s * seg, replica=rep)
             disk.core_position_vjp(ctx.ckpts[s], ctx.lam, ctx.cores[s], grad_rc[s], ybar)
         ga = pgrad[0].to(dtype=torch.as_tensor(ctx.alpha_like).dtype)
         gc = pgrad[1].to(dtype=torch.as_tensor(ctx.c_like).dtype)
@@ -79,6 +116,8 @@ class CoreTrajectory(torch.autograd.Function):
 
 def core_trajectory(m0, alpha, c, disk, params, n_seg, seg_steps, lambda_ex_nm, noise=None):
     """noise = None: RK4; noise = (seed, step0, replica): Heun with that Philox stream."""
+    if not torch.is_grad_enabled():               # no backward pass can follow: nothing to record
+        m0, alpha, c = (x.detach() if isinstance(x, torch.Tensor) else x for x in (m0, alpha, c))
     return CoreTrajectory.apply(m0, alpha, c, disk, params, n_seg, seg_steps, lambda_ex_nm, noise)
 
 
