@@ -383,6 +383,12 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
     if (rc) return rc;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    // A plan for every mode keeps to one workgroup of several unit groups per CU, whatever the occupancy
+    // query says.  Two of these (six wavefronts each, three on a SIMD, 168 of its 512 registers a lane) leave
+    // no slack: a disk's 40 workgroups placed on the 32 CUs of one XCD have waited for each other past the
+    // barrier's poll budget.  Nor do two pay: CUs that carry two next to CUs that carry one hold their disks
+    // up (16 disks of R = 40 nm with two unit groups: 43.5 us per RK4 step on 144 workgroups, 68.9 on 272).
+    if (modes == ALL_MODES && UG > 1) cap = std::min(cap, ncu);
     if (cap <= 0)
         return fail(LLG_EUNSUPPORTED, "no workgroup of " + std::to_string(WG_THREADS * UG) + " threads fits a CU with " +
                                           std::to_string(oc_lds) + " bytes of on-chip spectra");
@@ -469,11 +475,7 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         }
     } else {
         if (!(scale > 0.0 && scale <= 1.0)) return fail(LLG_EINVAL, "plan scale must be in (0, 1]");
-        // (the library's own plan keeps one workgroup of several groups per CU: CUs that carry two next to
-        // CUs that carry one hold their disks up; 16 disks of R = 40 nm with two unit groups: 43.5 us per RK4
-        // step on 144 workgroups, 68.9 on 272)
-        const int room = modes == ALL_MODES && UG > 1 ? std::min(cap, ncu) : cap;
-        const long long budget = std::max<long long>(sets[0].size(), (long long)std::floor(room * scale));
+        const long long budget = std::max<long long>(sets[0].size(), (long long)std::floor(cap * scale));
         for (const std::vector<int>& ids : sets) {
             double lo = 0.0, hi = 0.0;
             for (int k : ids) hi = std::max(hi, stage_time(k, 1));
