@@ -22,6 +22,7 @@ from dataclasses import replace
 
 import torch
 
+from ._lib import STEP_COUNTER
 from .api import Disk, LLGParams
 
 
@@ -66,7 +67,9 @@ class CoreTrajectory(torch.autograd.Function):
         cores = [disk.vortex_core_position(m, lambda_ex_nm)]
         recs = [None] * n_seg
         floats = _record_floats(disk, seg_steps, noise)
-        keep = _kept_segments(n_seg, floats, m.device) if any(ctx.needs_input_grad) and seg_steps > 0 else 0
+        keep = 0
+        if any(ctx.needs_input_grad) and seg_steps > 0 and (noise is None or noise[1] != STEP_COUNTER):
+            keep = _kept_segments(n_seg, floats, m.device)   # (a record needs explicit step indices)
         for s in range(n_seg):
             if s >= n_seg - keep:
                 recs[s] = torch.empty(floats, dtype=torch.float32, device=m.device)

@@ -359,11 +359,12 @@ int default_unit_groups(llg_disk h) {
 // by bisection.  Disks on chip (P <= h->onchip_pmax) take one workgroup each.
 //
 // With two rounds the call steps one half of the disks to its end before the
-// other, in a launch each on all workgroups: half as many disks share an XCD's L2, and
-// the row spectra that its workgroups exchange are more often still there (64
-// replicas of R = 250 nm, 1.6 MB of spectra each: 286 us per Heun step on 4
-// workgroups each, 265 in two rounds on 8; four rounds on 16 lose more to
-// uneven tiles than they gain).  Small disks do not gain: the ragged ensemble takes
+// other, in a launch each on all workgroups.  What that halves is the working
+// set: 3.8 MB of spectra and states per replica of R = 250 nm, 243 MB for 64 of
+// them and 122 MB for 32, next to 256 MB of memory-side cache; the bytes that
+// leave the L2s are the same either way (1.15 GB per Heun step).  286 us per step
+// on 4 workgroups each, 265 in two rounds on 8; four rounds on 16 lose more to
+// uneven tiles than they gain.  Small disks do not gain: the ragged ensemble takes
 // 357 us in one round, 400 in two.
 int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = ALL_MODES, double scale = 1.0,
          int rounds = 1) {
