@@ -1550,13 +1550,15 @@ constexpr int halo_floats(int PMAX) {
 
 // The integrators and the relaxation keep three wavefronts per SIMD resident (the
 // register budget the compiler must meet; a plan tuned for an integrator then
-// holds the relaxation too); the other modes take what they need.
-constexpr int min_waves_per_simd(int mode) {
-    return mode == MODE_RK4 || mode == MODE_HEUN || mode == MODE_RELAX ? 3 : 1;
+// holds the relaxation too); the other modes take what they need.  Workgroups of
+// two unit groups have a CU to themselves (six wavefronts, two on a SIMD), so
+// their instances may use 256 registers and need no scratch memory.
+constexpr int min_waves_per_simd(int mode, int UG) {
+    return mode == MODE_RK4 || mode == MODE_HEUN || mode == MODE_RELAX ? (UG == 2 ? 2 : 3) : 1;
 }
 
 template <int UG, int POL, int MODE, int PMAX, bool SER>
-__global__ __launch_bounds__(WG_THREADS* UG) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(MODE))))
+__global__ __launch_bounds__(WG_THREADS* UG) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd(MODE, UG))))
 void llg_persistent(KArgs a) {
     __shared__ float2 lds[LDS_FFT * UG];
     __shared__ float2 ltw[MAX_P];

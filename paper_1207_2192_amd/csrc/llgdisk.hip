@@ -305,6 +305,13 @@ int max_coresident_workgroups(int UG, int RSEL, int PMAX, int* out, unsigned mod
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, WG_THREADS * UG, dyn));
         per_cu = std::min(per_cu, b);
     }
+    // Workgroups of several unit groups: one per CU, whatever the query says.  Two of two unit groups (three
+    // wavefronts on a SIMD, 504 of its 512 registers a lane, scratch memory) were not held where a disk's
+    // workgroups shared an XCD: 40 on the 32 CUs of one, and 33, waited for each other past the barrier's poll
+    // budget.  Nor do two pay: CUs that carry two next to CUs that carry one hold their disks up (16 disks of
+    // R = 40 nm: 43.5 us per RK4 step on 144 workgroups, 68.9 on 272; 64 replicas of R = 250 nm: 377 us per
+    // Heun step on 512 against 293 with four unit groups on 256).
+    if (UG > 1) per_cu = std::min(per_cu, 1);
     *out = ncu * per_cu;
     return 0;
 }
@@ -379,17 +386,9 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         oc[k] = h->onchip_pmax > 0 && h->P[k] <= h->onchip_pmax;
         if (oc[k]) oc_lds = std::max(oc_lds, (unsigned)(3 * (h->P[k] / 2 + 1) * h->desc[k].Dp * sizeof(float2)));
     }
-    int cap = 0, dev = 0, ncu = 0;
+    int cap = 0;
     int rc = max_coresident_workgroups(UG, RSEL, h->PMAX, &cap, modes, oc_lds);
     if (rc) return rc;
-    HIP_TRY(hipGetDevice(&dev));
-    HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    // A plan for every mode keeps to one workgroup of several unit groups per CU, whatever the occupancy
-    // query says.  Two of these (six wavefronts each, three on a SIMD, 168 of its 512 registers a lane) leave
-    // no slack: a disk's 40 workgroups placed on the 32 CUs of one XCD have waited for each other past the
-    // barrier's poll budget.  Nor do two pay: CUs that carry two next to CUs that carry one hold their disks
-    // up (16 disks of R = 40 nm with two unit groups: 43.5 us per RK4 step on 144 workgroups, 68.9 on 272).
-    if (modes == ALL_MODES && UG > 1) cap = std::min(cap, ncu);
     if (cap <= 0)
         return fail(LLG_EUNSUPPORTED, "no workgroup of " + std::to_string(WG_THREADS * UG) + " threads fits a CU with " +
                                           std::to_string(oc_lds) + " bytes of on-chip spectra");
