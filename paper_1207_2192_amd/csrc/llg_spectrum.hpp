@@ -11,6 +11,9 @@
 // crosses memory once.  Radix-2 passes through global memory, one launch each,
 // took 71 us for 96 sequences of 4096 points (15 launches of 3-5 us); one
 // launch takes 12.9 us, call to call, bound by the latency of its passes.
+// Error against extended precision, root mean square of the norm over 64 recorded
+// sequences: 1.3e-16 to 1.5e-16 at every length from 16 to 65536 samples; the
+// radix-2 passes had 1.5e-16 to 2.0e-16.
 // Longer: M = M1 x M2; ps_cols transforms the M1-point columns (several
 // columns per workgroup, so that the loads stay coalesced) and applies the
 // twiddles between the two factors, ps_rows the M2-point rows, ps_separate
@@ -54,10 +57,11 @@ __device__ __forceinline__ void zdft(double2* x) {
         double2 e[4] = {x[0], x[2], x[4], x[6]}, o[4] = {x[1], x[3], x[5], x[7]};
         zdft<4>(e);
         zdft<4>(o);
-        const double r = 0.70710678118654752440;
-        const double2 t1 = make_double2(r * (o[1].x + o[1].y), r * (o[1].y - o[1].x));
+        // times sqrt(1/2) with what the constant lacks: its rounding scales a whole line of the spectrum alike
+        auto half = [](double v) { return fma(0.70710678118654752440, v, -4.833646656726457e-17 * v); };
+        const double2 t1 = make_double2(half(o[1].x + o[1].y), half(o[1].y - o[1].x));
         const double2 t2 = zrot(o[2]);
-        const double2 t3 = make_double2(r * (o[3].y - o[3].x), -r * (o[3].x + o[3].y));
+        const double2 t3 = make_double2(half(o[3].y - o[3].x), -half(o[3].x + o[3].y));
         x[0] = zadd(e[0], o[0]);
         x[4] = zsub(e[0], o[0]);
         x[1] = zadd(e[1], t1);
@@ -108,15 +112,12 @@ __device__ __forceinline__ void ps_store_pass(double2* buf, double2 (&v)[8], int
         if (b >= TOTAL) continue;
         const int c = b / PER, t = b % PER, kk = t & (Ns - 1);
         double2* x = v + q * R;
-        if (Ns > 1) {
-            const double2 w = zroot(kk, (long long)Ns * R);
-            double2 p = w;
+        // Every factor from the sine.  As a chain of products of the first one (12.9 us for 96 sequences of 8192, 17.4
+        // this way; 12.9 both for 4096) they double the spectra's error, and a tree of products does so too; w, w^2
+        // and w^4 from the sine and products of those (15.3 us) stay 5 % above the radix-2 passes at some lengths.
+        if (Ns > 1)
 #pragma unroll
-            for (int j = 1; j < R; ++j) {
-                x[j] = zmul(x[j], p);
-                p = zmul(p, w);
-            }
-        }
+            for (int j = 1; j < R; ++j) x[j] = zmul(x[j], zroot(j * kk, (long long)Ns * R));
         zdft<R>(x);
         const int base = c * S::M + (t - kk) * R + kk;
 #pragma unroll
@@ -155,15 +156,40 @@ __device__ __forceinline__ double2 ps_point(const double* xb, long long n, long 
     return z;
 }
 
+// A value with the rounding of the operations that gave it.
+struct Exact2 {
+    double v, e;
+};
+__device__ __forceinline__ Exact2 exact_sum(double a, double b) {   // Knuth's two-sum
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+
 // |X_k|^2 / len and |X_M-k|^2 / len from a = Z_k and b = Z_M-k (M = len / 2):
 // X_k = E + W O and X_M-k = conj(E - W O) with E = (a + conj b)/2, O = (a - conj b)/(2i), W = exp(-2 pi i k / len).
+// The packed transform takes one level of additions more here than a transform
+// of the len real samples, and the roundings of the last levels are the ones that
+// reach a spectral line undivided; so this one carries them along and rounds once.
 __device__ __forceinline__ void ps_pair(double2 a, double2 b, long long k, long long len, double& pk, double& pm) {
-    const double2 E = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
-    const double2 O = make_double2(0.5 * (a.y + b.y), -0.5 * (a.x - b.x));
-    const double2 t = zmul(zroot(k, len), O);
-    const double2 u = zadd(E, t), w = zsub(E, t);
-    pk = (u.x * u.x + u.y * u.y) / (double)len;
-    pm = (w.x * w.x + w.y * w.y) / (double)len;
+#pragma clang fp contract(off)
+    const Exact2 Ex = exact_sum(0.5 * a.x, 0.5 * b.x), Ey = exact_sum(0.5 * a.y, -0.5 * b.y);
+    const Exact2 Ox = exact_sum(0.5 * a.y, 0.5 * b.y), Oy = exact_sum(0.5 * b.x, -0.5 * a.x);
+    const double2 W = zroot(k, len);
+    auto add2 = [](Exact2 z, double p, Exact2 x, double q, Exact2 y) {   // z + p x + q y
+        const double px = p * x.v, qy = q * y.v;
+        const Exact2 s = exact_sum(px, qy), t = exact_sum(z.v, s.v);
+        const double e = (fma(p, x.v, -px) + fma(q, y.v, -qy)) + (p * x.e + q * y.e);
+        return Exact2{t.v, t.e + (s.e + (z.e + e))};
+    };
+    auto power = [len](Exact2 x, Exact2 y) {
+        const double xx = x.v * x.v, yy = y.v * y.v;
+        const Exact2 s = exact_sum(xx, yy);
+        if (!isfinite(s.v)) return s.v;
+        const double e = (fma(x.v, x.v, -xx) + fma(y.v, y.v, -yy)) + 2.0 * (x.v * x.e + y.v * y.e);
+        return (s.v + (s.e + e)) / (double)len;
+    };
+    pk = power(add2(Ex, W.x, Ox, -W.y, Oy), add2(Ey, W.y, Ox, W.x, Oy));
+    pm = power(add2(Ex, -W.x, Ox, W.y, Oy), add2(Ey, -W.y, Ox, -W.x, Oy));
 }
 
 // Sum over a workgroup of THREADS threads (every thread gets it).
