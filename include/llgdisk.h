@@ -240,7 +240,8 @@ int llg_heun_series(llg_disk h, float* m, long long nsteps, unsigned long long s
  * X_b[k] = sum_t w[t] x_b[t] exp(-2 pi i t k / len) and
  * out[b * (len/2 + 1) + k] = |X_b[k]|^2 / len for k = 0 .. len/2 (device).
  * len must be a power of two in [16, 2^24].  work (device) holds 4 * len * n_seq
- * doubles.  float64 throughout. */
+ * doubles and must not overlap x; out may overlap x (which is read whole before
+ * out is written) or lie in work.  float64 throughout. */
 int llg_power_spectrum(const double* x, int n_seq, long long bstride, long long len, long long tstride,
                        int remove_mean, int window, double* work, double* out, void* stream);
 

@@ -256,6 +256,11 @@ __global__ __launch_bounds__((PsShape<LOGM, 0>::THREADS)) void ps_whole(const do
     }
 }
 
+// Spectra from the workspace to a result array that overlaps the input.
+__global__ __launch_bounds__(256) void ps_copy(const double* from, long long n, double* to) {
+    for (long long q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (long long)gridDim.x * 256) to[q] = from[q];
+}
+
 // Mean of each sequence (or 0), for the sequences that take several workgroups.
 __global__ __launch_bounds__(1024) void ps_mean(const double* x, long long bstride, long long len, long long tstride,
                                                 int remove_mean, double* mean) {

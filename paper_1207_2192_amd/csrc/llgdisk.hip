@@ -1370,10 +1370,22 @@ int llg_power_spectrum(const double* x, int n_seq, long long bstride, long long 
     if (window != 0 && window != 1) return fail(LLG_EINVAL, "window: 0 = none, 1 = Hann");
     hipStream_t st = (hipStream_t)stream;
     const int logm = (int)std::lround(std::log2((double)len)) - 1;
-    if (logm <= PS_MAX_LOGM)
+    const long long n_out = n_seq * (len / 2 + 1), n_x = (n_seq - 1) * bstride + (len - 1) * tstride + 1;
+    auto meet = [](const double* a, long long na, const double* b, long long nb) {
+        return (uintptr_t)a < (uintptr_t)(b + nb) && (uintptr_t)b < (uintptr_t)(a + na);
+    };
+    // the half of work that out stays clear of (it is shorter than the gap between the parts used of either)
+    double* const part = meet(out, n_out, work, (len + 1) * n_seq) ? work + 2 * len * n_seq : work;
+    if (logm > PS_MAX_LOGM) {
+        spectrum_split(logm, x, n_seq, bstride, len, tstride, remove_mean, window, part, out, st);
+    } else if (meet(out, n_out, x, n_x)) {   // every sequence is read before the first spectrum reaches out
+        spectrum_whole(logm, x, n_seq, bstride, tstride, remove_mean, window, part, st);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(ps_copy, dim3((unsigned)std::min<long long>((n_out + 255) / 256, 4096)), dim3(256), 0, st,
+                           part, n_out, out);
+    } else {
         spectrum_whole(logm, x, n_seq, bstride, tstride, remove_mean, window, out, st);
-    else
-        spectrum_split(logm, x, n_seq, bstride, len, tstride, remove_mean, window, work, out, st);
+    }
     HIP_TRY(hipGetLastError());
     return 0;
 }
