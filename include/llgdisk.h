@@ -354,6 +354,14 @@ int llg_last_launch_ms(llg_disk h, int mode, float* ms);
  * launch that timed out are unspecified. */
 int llg_debug_spin_limit(llg_disk h, unsigned int polls);
 
+/* Plan test hook (host): re-plan like llg_tune with the library's workgroup
+ * counts, the calls of a persistent launch stepping the disks in `rounds` (up to
+ * the number of disks) launches one after the other, large and small disks dealt
+ * to them in turn, as llg_autotune does for many large disks where two are
+ * faster; 0 leaves the plan as it is.  Returns the launches of the plan in force
+ * (or an error). */
+int llg_debug_rounds(llg_disk h, int unit_groups, int radix_policy, int rounds);
+
 /* The noise w that llg_heun_step uses at one time step (test hook), packed
  * like m (zero outside the disks). */
 int llg_noise(llg_disk h, unsigned long long seed, unsigned long long step,

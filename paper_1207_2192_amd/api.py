@@ -168,6 +168,15 @@ class Disk:
         launches give up after `polls` polls; 0 restores the default."""
         check(_lib.load().llg_debug_spin_limit(self._h, int(polls)), "llg_debug_spin_limit")
 
+    def debug_rounds(self, unit_groups: int = 1, radix_policy: int = 0, rounds: int = 0) -> int:
+        """Plan test hook (llg_debug_rounds): the disks stepped in `rounds` launches one
+        after the other (0: the plan stays); returns the launches of the plan in force."""
+        lib = _lib.load()
+        got = lib.llg_debug_rounds(self._h, int(unit_groups), int(radix_policy), int(rounds))
+        check(min(got, 0), "llg_debug_rounds")
+        self.workgroups = [lib.llg_disk_workgroups(self._h, k) for k in range(self.n)]
+        return got
+
     @property
     def on_chip(self) -> int:
         """The max_P of the on-chip spectra plan (0: none)."""

@@ -1060,6 +1060,18 @@ int llg_tune(llg_disk h, int unit_groups, int radix_policy, const int* wg_per_di
     return 0;
 }
 
+int llg_debug_rounds(llg_disk h, int unit_groups, int radix_policy, int rounds) {
+    int rc = check_handle(h);
+    if (rc) return rc;
+    if (rounds < 0 || rounds > h->n) return fail(LLG_EINVAL, "rounds must be between 0 and the number of disks");
+    if (rounds > 0) {
+        HIP_TRY(hipDeviceSynchronize());
+        if ((rc = plan(h, unit_groups, radix_policy, nullptr, ALL_MODES, 1.0, rounds))) return rc;
+        h->resident = false;
+    }
+    return h->rounds;
+}
+
 int llg_set_on_chip(llg_disk h, int max_P) {
     int rc = check_handle(h);
     if (rc) return rc;
@@ -1459,8 +1471,8 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
     zp.gridDim = dim3((h->n_bars + 255) / 256);
     zp.blockDim = dim3(256);
     zp.kernelParams = zargs;
-    hipGraphNode_t nz, np, na;
-    if (!h->resident) HIP_TRY(hipGraphAddKernelNode(&nz, g->graph, nullptr, 0, &zp));
+    hipGraphNode_t last = nullptr, next = nullptr;   // the nodes form a chain; a call's result never replaces its input
+    if (!h->resident) HIP_TRY(hipGraphAddKernelNode(&last, g->graph, nullptr, 0, &zp));
     // node 2: the persistent cooperative launch
     const int mode = integrator == 0 ? MODE_RK4 : MODE_HEUN;
     KArgs a = make_args(h, gprm, mode, m, nullptr, nsteps, seed, 0, replica, integrator == 1 ? h->step_dev : nullptr,
@@ -1480,15 +1492,16 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
         kp.gridDim = dim3(h->n);
         kp.blockDim = dim3(RES_THREADS);
         kp.sharedMemBytes = 0;
-        HIP_TRY(hipGraphAddKernelNode(&np, g->graph, nullptr, 0, &kp));
+        HIP_TRY(hipGraphAddKernelNode(&last, g->graph, nullptr, 0, &kp));
     } else {
         hipKernelNodeAttrValue coop{};
         coop.cooperative = 1;
         for (int r = 0; r < h->rounds; ++r) {   // the rounds of the plan, one after the other
             a.wg2disk = gw2d + (size_t)r * h->n_wg;
             a.wg2local = gw2l + (size_t)r * h->n_wg;
-            HIP_TRY(hipGraphAddKernelNode(&np, g->graph, r == 0 ? &nz : &np, 1, &kp));
-            HIP_TRY(hipGraphKernelNodeSetAttribute(np, hipKernelNodeAttributeCooperative, &coop));
+            HIP_TRY(hipGraphAddKernelNode(&next, g->graph, &last, 1, &kp));
+            HIP_TRY(hipGraphKernelNodeSetAttribute(next, hipKernelNodeAttributeCooperative, &coop));
+            last = next;
         }
     }
     // node 3 (Heun): advance the step counter so that the next replay continues the noise stream
@@ -1501,7 +1514,7 @@ int llg_graph_create(llg_disk h, int integrator, float* m, long long nsteps, con
         ap.gridDim = dim3(1);
         ap.blockDim = dim3(64);
         ap.kernelParams = aargs;
-        HIP_TRY(hipGraphAddKernelNode(&na, g->graph, &np, 1, &ap));
+        HIP_TRY(hipGraphAddKernelNode(&next, g->graph, &last, 1, &ap));
     }
     HIP_TRY(hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0));
     *out = g.release();
