@@ -690,7 +690,8 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         d.mask = g.mask;
         d.tw = h->twiddles[d.P];
     }
-    if ((rc = plan(h, default_unit_groups(h), 0, wg_per_disk))) return rc;
+    // explicit counts are counts of one unit group, the most a disk can use
+    if ((rc = plan(h, wg_per_disk ? 1 : default_unit_groups(h), 0, wg_per_disk))) return rc;
     plan_field(h);
     if ((rc = h->dalloc(&h->field_part, (size_t)n * h->field_g[2] * PART_STRIDE))) return rc;
     // explicit workgroup counts ask for the persistent plan; otherwise small disks are resident (R = 30 nm: one disk
