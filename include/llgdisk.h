@@ -168,9 +168,10 @@ int llg_tune(llg_disk h, int unit_groups, int radix_policy, const int* wg_per_di
  * one group of three wavefronts per workgroup.  Re-plans like llg_tune with
  * the current unit groups and transform policy and the library's workgroup
  * counts (host; synchronises the device); llg_tune and llg_autotune keep the
- * setting.  Fails with LLG_EUNSUPPORTED, leaving the previous plan, when the
- * current plan has more than one unit group (and so does llg_tune asking for
- * more than one while a limit is set).
+ * setting.  Fails with LLG_EUNSUPPORTED, leaving the previous plan, when
+ * llg_tune or llg_autotune gave the current plan more than one unit group (and
+ * so does llg_tune asking for more than one while a limit is set); where they
+ * are the library's own choice, a limit takes them back to one.
  * Results are bitwise those of the same plan with the spectra in global
  * memory.  llg_get_on_chip returns the current max_P. */
 int llg_set_on_chip(llg_disk h, int max_P);

@@ -191,6 +191,7 @@ struct llg_disk_s {
     unsigned plan_modes = 0;          // modes whose co-residency the current plan was checked for
     unsigned plan_series_modes = 0;   // the same for the series instances of the integrators
     int UG = 1;                       // wavefront groups per workgroup of the persistent launch
+    bool default_ug = true;           // UG is the library's choice
     int RSEL = 0;                     // transform policy (radix and column strategy)
     int PMAX = 256;                   // largest FFT size of the handle's disks (kernel instance)
     bool field_wide = false;          // field kernels: shape for many tiles per CU
@@ -690,7 +691,7 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
         d.mask = g.mask;
         d.tw = h->twiddles[d.P];
     }
-    // explicit counts are counts of one unit group, the most a disk can use
+    h->default_ug = !wg_per_disk;   // explicit counts are counts of one unit group, the most a disk can use
     if ((rc = plan(h, wg_per_disk ? 1 : default_unit_groups(h), 0, wg_per_disk))) return rc;
     plan_field(h);
     if ((rc = h->dalloc(&h->field_part, (size_t)n * h->field_g[2] * PART_STRIDE))) return rc;
@@ -1057,7 +1058,7 @@ int llg_tune(llg_disk h, int unit_groups, int radix_policy, const int* wg_per_di
     if (rc) return rc;
     HIP_TRY(hipDeviceSynchronize());
     if ((rc = plan(h, unit_groups, radix_policy, wg_per_disk))) return rc;
-    h->resident = false;
+    h->resident = h->default_ug = false;
     return 0;
 }
 
@@ -1068,7 +1069,7 @@ int llg_debug_rounds(llg_disk h, int unit_groups, int radix_policy, int rounds) 
     if (rounds > 0) {
         HIP_TRY(hipDeviceSynchronize());
         if ((rc = plan(h, unit_groups, radix_policy, nullptr, ALL_MODES, 1.0, rounds))) return rc;
-        h->resident = false;
+        h->resident = h->default_ug = false;
     }
     return h->rounds;
 }
@@ -1080,7 +1081,9 @@ int llg_set_on_chip(llg_disk h, int max_P) {
     HIP_TRY(hipDeviceSynchronize());
     const int old = h->onchip_pmax;
     h->onchip_pmax = max_P;
-    if ((rc = plan(h, h->UG, h->RSEL, nullptr))) {
+    // spectra on chip take one unit group; several are refused where the caller or the tuner chose them
+    const int ug = !h->default_ug ? h->UG : max_P ? 1 : default_unit_groups(h);
+    if ((rc = plan(h, ug, h->RSEL, nullptr))) {
         h->onchip_pmax = old;   // the previous plan stays in force
         return rc;
     }
@@ -1200,6 +1203,7 @@ int llg_autotune(llg_disk h, const float* m, const llg_params* p, int integrator
     }
     h->onchip_pmax = bestc.oc;
     h->resident = bestc.resident;
+    h->default_ug = false;
     const unsigned modes = bestc.resident ? ALL_MODES : 1u << mode;
     if ((rc = plan(h, bestc.UG, bestc.RSEL, nullptr, modes, bestc.scale, bestc.rounds))) return rc;
     if (best_us) *best_us = best * 1e3 / (double)probe_steps;
