@@ -535,7 +535,7 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         DiskDesc& d = h->desc[k];
         d.bar = h->bars + h->n_bars;
         d.bar_lines = bar_lines_for(G[k]);
-        h->n_bars += d.bar_lines * BAR_STRIDE;
+        h->n_bars += d.bar_lines * LINE_STRIDE;
         h->dfree(d.part);
         d.part = nullptr;
         if ((rc = h->dalloc(&d.part, (size_t)PART_STRIDE * G[k]))) return rc;
@@ -654,7 +654,7 @@ int create(int n, const double* R_nm, const double* L_nm, double a_nm, const int
     // ---- per-disk workspaces
     int rc = 0;
     // room for any plan (a graph keeps using the counters of its own)
-    if ((rc = h->dalloc(&h->bars, (size_t)n * BAR_LINES * BAR_STRIDE))) return rc;
+    if ((rc = h->dalloc(&h->bars, (size_t)n * BAR_LINES * LINE_STRIDE))) return rc;
     if ((rc = h->dalloc(&h->err_dev, 1))) return rc;
     HIP_TRY(hipMemset(h->err_dev, 0, sizeof(int)));
     if ((rc = h->dalloc(&h->step_dev, 1))) return rc;
