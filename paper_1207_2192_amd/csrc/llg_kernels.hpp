@@ -480,9 +480,14 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     constexpr int NWV = 3 * UG;                  // wavefronts of the workgroup
     constexpr int VW = HC >= 64 ? HC / 64 : 1;   // columns per lane and row
     constexpr int HQ = (3 * HR + NWV - 1) / NWV; // rounds of rows
-    constexpr int IH = OPQ ? HQ * VW : (3 * HR * HC + NT - 1) / NT;
+    // (A row of P = 64 fills half a wavefront: there the relaxation and the RK4 adjoint
+    // run over elements too, five loads a thread instead of ten.  20 sweeps of one
+    // D = 12 disk 263 us with rows, 225 now; the adjoint of 4 steps 226, 209.)
+    constexpr bool GRAD_OR_RELAX = MODE == MODE_RELAX || MODE == MODE_RK4_VJP;
+    constexpr bool ROWS = OPQ && !(GRAD_OR_RELAX && HC < 64);
+    constexpr int IH = ROWS ? HQ * VW : (3 * HR * HC + NT - 1) / NT;
     auto halo_elem = [&](int q, int& row, int& i) {
-        if constexpr (OPQ) {
+        if constexpr (ROWS) {
             row = __builtin_amdgcn_readfirstlane(tid<OPQ>() >> 6) + (q / VW) * NWV;
             i = (tid<OPQ>() & 63) + 64 * (q % VW);
         } else {
@@ -597,9 +602,13 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     // Cell-update item idx -> (row pair uu of the iteration, column i).  Where
     // the index arithmetic is recomputed inside the loop (OPQ) the columns sit on
     // a stride of P/2 (shifts, no division by D); where it is hoisted, on a
-    // stride of D (fewer idle items).
+    // stride of D (fewer idle items).  So they do in the relaxation and the RK4
+    // adjoint of radix-8 plans at P <= 128, whose tiles of four or eight row pairs
+    // need a second round of items on the stride of P/2 (four disks of D = 20: 356 us
+    // for the adjoint of 4 steps, 301 now; D = 48: 370, 345; at P = 256 no different).
+    constexpr bool SHIFT = OPQ && !(GRAD_OR_RELAX && R == 8 && P <= 128);
     auto cell_item = [&](int idx, int& uu, int& i) {
-        if constexpr (OPQ) {
+        if constexpr (SHIFT) {
             uu = idx / (P / 2);
             i = idx % (P / 2);
             return uu < U && i < D;
@@ -1303,16 +1312,22 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             column_pass();
             if (!group_barrier(d.bar, d.bar_lines, ++epoch, g, G, a.err, a.spin_limit)) return;
             for (int q = 0; q < 8; ++q) rq[q] = 0.0;
-            // the next iteration's staged rows and spectra are in flight during this one's transforms
+            // the next iteration's staged rows and spectra are in flight during this one's transforms; past
+            // the last iteration nothing is loaded (a workgroup with one tile of P = 64 spent 1 of 12 us a sweep
+            // on it; 4 disks of D = 250: 537 -> 504 us for 20 sweeps)
             if (g < n_rb) {
                 float hv[IH];
                 SRow sv[IS];
                 halo_load(g, cur, hv, sweep == 0);   // only the caller's state needs the disk test
                 row_load(g, sv);
-                for (int b = g; b < n_rb; b += G) {
+                for (int b = g;; b += G) {
                     halo_store(hv);
                     row_unpack_inverse(sv);
                     relax_update(b, nxt, lx, ly, Xc, Yc);
+                    if (b + G >= n_rb) {
+                        row_forward_store(b);
+                        break;
+                    }
                     halo_load(b + G, cur, hv, sweep == 0);
                     row_load(b + G, sv);
                     row_forward_store(b);
