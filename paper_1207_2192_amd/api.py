@@ -66,6 +66,11 @@ class LLGParams:
             return bytes(self.to_c())
 
 
+def _packed(p) -> bytes:
+    """One llg_params of any object with a to_c(), which a class may define for itself."""
+    return p.to_bytes() if getattr(type(p), "to_c", None) is LLGParams.to_c else bytes(p.to_c())
+
+
 def params_from_si(A: float, Ms: float, gamma: float, a_nm: float, L_nm: float, dt_ps: float,
                    T_K: float = 0.0, alpha: float = 0.0):
     """(LLGParams, lambda_ex_nm) from SI material data via llg_params_from_si."""
@@ -212,11 +217,11 @@ class Disk:
 
     def _params(self, params):
         if isinstance(params, LLGParams):
-            data = params.to_bytes() * self.n
+            data = _packed(params) * self.n
         else:
             if len(params) != self.n:
                 raise ValueError(f"need {self.n} parameter sets")
-            data = b"".join([p.to_bytes() for p in params])
+            data = b"".join([_packed(p) for p in params])
         return (LLGParamsC * self.n).from_buffer_copy(data)
 
     def unpack(self, flat: torch.Tensor, k: int) -> torch.Tensor:
