@@ -54,9 +54,16 @@ def _record(disk: Disk, m, seg_steps: int, prm, noise, s: int, rec):
 
 
 class CoreTrajectory(torch.autograd.Function):
+    @classmethod
+    def apply(cls, *args):
+        # forward always runs with gradients off, so the caller's mode goes along: without gradients no
+        # backward pass can follow, and nothing is recorded
+        noise = (None,) if len(args) == 8 else ()
+        return super().apply(*args, *noise, torch.is_grad_enabled())
+
     @staticmethod
     def forward(ctx, m0, alpha, c, disk: Disk, params: LLGParams, n_seg: int, seg_steps: int,
-                lambda_ex_nm: float, noise=None):
+                lambda_ex_nm: float, noise, grad_enabled: bool):
         if disk.n != 1:
             raise ValueError("CoreTrajectory steps one disk")
         if noise is None and params.renorm:
@@ -68,7 +75,7 @@ class CoreTrajectory(torch.autograd.Function):
         recs = [None] * n_seg
         floats = _record_floats(disk, seg_steps, noise)
         keep = 0
-        if any(ctx.needs_input_grad) and seg_steps > 0 and (noise is None or noise[1] != STEP_COUNTER):
+        if grad_enabled and any(ctx.needs_input_grad) and seg_steps > 0 and (noise is None or noise[1] != STEP_COUNTER):
             keep = _kept_segments(n_seg, floats, m.device)   # (a record needs explicit step indices)
         for s in range(n_seg):
             if s >= n_seg - keep:
@@ -114,13 +121,11 @@ class CoreTrajectory(torch.autograd.Function):
             ga = ga.to(ctx.alpha_like.device)
         if isinstance(ctx.c_like, torch.Tensor):
             gc = gc.to(ctx.c_like.device)
-        return ybar, ga, gc, None, None, None, None, None, None
+        return ybar, ga, gc, None, None, None, None, None, None, None
 
 
 def core_trajectory(m0, alpha, c, disk, params, n_seg, seg_steps, lambda_ex_nm, noise=None):
     """noise = None: RK4; noise = (seed, step0, replica): Heun with that Philox stream."""
-    if not torch.is_grad_enabled():               # no backward pass can follow: nothing to record
-        m0, alpha, c = (x.detach() if isinstance(x, torch.Tensor) else x for x in (m0, alpha, c))
     return CoreTrajectory.apply(m0, alpha, c, disk, params, n_seg, seg_steps, lambda_ex_nm, noise)
 
 

@@ -1,0 +1,57 @@
+"""When a trajectory's forward pass keeps stage records, on a disk that only counts its
+calls (no GPU)."""
+import pytest
+import torch
+
+from paper_1207_2192_amd import LLGParams, adjoint
+
+
+class Counting:
+    """The calls of a Disk that a trajectory makes; states pass through unchanged."""
+    n, state_size = 1, 12
+
+    def __init__(self):
+        self.calls = []
+
+    def _state(self, m):
+        return m
+
+    def vortex_core_position(self, m, lam):
+        return torch.zeros(1, 5, dtype=torch.float64)
+
+    def core_position_vjp(self, *a):
+        pass
+
+    def __getattr__(self, name):
+        def call(*a, **kw):
+            self.calls.append((name, kw.get("step0")))
+        return call
+
+    def count(self, name):
+        return sum(n == name for n, _ in self.calls)
+
+
+@pytest.fixture(autouse=True)
+def memory(monkeypatch):
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (200 << 30, 288 << 30))
+
+
+def run(disk, noise=None, function=None, n_seg=3, seg=2):
+    m = torch.zeros(disk.state_size, requires_grad=True)
+    a, c = (torch.tensor(v, dtype=torch.float64, requires_grad=True) for v in (0.1, 0.2))
+    args = (m, a, c, disk, LLGParams(), n_seg, seg, 5.0)
+    return (function or adjoint.core_trajectory)(*args, *([noise] if noise else []))
+
+
+@pytest.mark.parametrize("function", [adjoint.core_trajectory, adjoint.CoreTrajectory.apply])
+@pytest.mark.parametrize("mode", [torch.no_grad, torch.inference_mode])
+def test_nothing_is_recorded_where_gradients_are_off(function, mode):
+    disk = Counting()
+    with mode():
+        rc = run(disk, function=function)
+    assert rc.shape[0] == 4 and not rc.requires_grad
+    assert disk.count("rk4_record") == 0 and disk.count("rk4_step") == 3
+    rc = run(disk, function=function)
+    assert rc.requires_grad and disk.count("rk4_record") == 3 and disk.count("rk4_step") == 3
+    rc.sum().backward()
+    assert disk.count("rk4_vjp") == 3 and disk.count("rk4_record") == 3
