@@ -44,6 +44,12 @@ def _record_floats(disk: Disk, seg_steps: int, noise) -> int:
     return (8 if noise is None else 4) * seg_steps * disk.state_size
 
 
+def _explicit_steps(noise, s: int, seg_steps: int) -> bool:
+    """Whether segment s can be recorded: a first step index that is STEP_COUNTER as 64
+    bits stands for the handle's counter, which plain steps take and a record does not."""
+    return noise is None or (int(noise[1]) + s * seg_steps) % 2 ** 64 != STEP_COUNTER
+
+
 def _record(disk: Disk, m, seg_steps: int, prm, noise, s: int, rec):
     """Segment s of the trajectory in place, with its stage record."""
     if noise is None:
@@ -75,10 +81,10 @@ class CoreTrajectory(torch.autograd.Function):
         recs = [None] * n_seg
         floats = _record_floats(disk, seg_steps, noise)
         keep = 0
-        if grad_enabled and any(ctx.needs_input_grad) and seg_steps > 0 and (noise is None or noise[1] != STEP_COUNTER):
-            keep = _kept_segments(n_seg, floats, m.device)   # (a record needs explicit step indices)
+        if grad_enabled and any(ctx.needs_input_grad) and seg_steps > 0:
+            keep = _kept_segments(n_seg, floats, m.device)
         for s in range(n_seg):
-            if s >= n_seg - keep:
+            if s >= n_seg - keep and _explicit_steps(noise, s, seg_steps):
                 recs[s] = torch.empty(floats, dtype=torch.float32, device=m.device)
                 _record(disk, m, seg_steps, prm, noise, s, recs[s])
             elif noise is None:

@@ -55,3 +55,11 @@ def test_nothing_is_recorded_where_gradients_are_off(function, mode):
     assert rc.requires_grad and disk.count("rk4_record") == 3 and disk.count("rk4_step") == 3
     rc.sum().backward()
     assert disk.count("rk4_vjp") == 3 and disk.count("rk4_record") == 3
+
+
+@pytest.mark.parametrize("step0,counter", [(5, None), (-1, 0), (2 ** 64 - 1, 0), (2 ** 64 - 5, 2), (-3, 1)])
+def test_a_segment_on_the_step_counter_is_stepped_plainly(step0, counter):
+    disk = Counting()
+    run(disk, noise=(7, step0, 0))
+    want = [("heun_step" if s == counter else "heun_record", step0 + 2 * s) for s in range(3)]
+    assert disk.calls == want
