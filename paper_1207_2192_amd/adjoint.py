@@ -7,17 +7,19 @@ on the GPU and returns the vortex core position r_c (nm, float64) at the
 n_seg + 1 checkpoints t = 0, seg_steps, ...  Checkpoints of the state are kept
 every seg_steps steps.  Where a gradient is asked for, the forward pass steps with
 the stage record (llg_rk4_record / llg_heun_record) and keeps it for as many
-segments as RECORD_SHARE of the device's memory holds (5000 RK4 steps at R = 80 nm:
-3 GB of 288); the backward pass recomputes the record of the others from their
-checkpoints.  It runs the reverse sweep
-(llg_rk4_vjp / llg_heun_vjp, the noise replayed from its counter); the
-cotangent of each sampled core position enters through llg_core_position_vjp.
+segments as RECORD_SHARE of the device's memory holds beside those of the other
+trajectories that wait for theirs (5000 RK4 steps at R = 80 nm: 3 GB of 288); the
+backward pass recomputes the record of the others from their checkpoints.  It
+runs the reverse sweep (llg_rk4_vjp / llg_heun_vjp, the noise replayed from its
+counter); the cotangent of each sampled core position enters through
+llg_core_position_vjp.
 Gradients come out for m0, alpha and c = a^2/lambda_ex^2;
 `grad_exchange_length` converts d/dc into d/d lambda_ex.  All arithmetic runs
 in lib_llgdisk; torch provides buffers and the stream.
 """
 from __future__ import annotations
 
+import threading
 from dataclasses import replace
 
 import torch
@@ -26,18 +28,51 @@ from ._lib import STEP_COUNTER
 from .api import Disk, LLGParams
 
 
-# Records are kept between the passes up to this share of the device's memory (18 GB
-# of 288) and half of what is free.  A recorded RK4 step costs 36.3 us against 35.7
-# plain at R = 80 nm (17.1 against 16.3 at 30 nm), so recomputing a segment is a
-# whole forward pass over: 2 x 50 steps at R = 80 nm, forward and backward, 13.5 ms
-# recomputed and 10.2 ms kept.
+# Records are kept between the passes, by all trajectories of the process together, up
+# to RECORD_SHARE of the device's memory (18 GB of 288), and by one up to FREE_SHARE of
+# what is free.  A recorded RK4 step costs 36.3 us against 35.7 plain at R = 80 nm (17.1
+# against 16.3 at 30 nm), so recomputing a segment is a whole forward pass over: 2 x 50
+# steps at R = 80 nm, forward and backward, 13.5 ms recomputed and 10.2 ms kept.
 RECORD_SHARE = 1.0 / 16
+FREE_SHARE = 1.0 / 8
+
+
+class _Record:
+    """A segment's record, counted against the device's share until it is dropped."""
+    held: dict = {}                 # bytes kept, by device
+    lock = threading.RLock()        # taken again by a drop that a collection inside it causes
+
+    def __init__(self, floats: int, device):
+        self.device, self.bytes = device, 0
+        self.data = torch.empty(floats, dtype=torch.float32, device=device)
+        self.bytes = 4 * floats
+        with self.lock:
+            self.held[device] = self.held.get(device, 0) + self.bytes
+
+    def __del__(self):
+        with self.lock:
+            self.held[self.device] = self.held.get(self.device, 0) - self.bytes
 
 
 def _kept_segments(n_seg: int, seg_floats: int, device) -> int:
     """Segments whose record the forward pass may keep until the backward pass."""
     free, total = torch.cuda.mem_get_info(device)
-    return max(0, min(n_seg, int(min(RECORD_SHARE * total, 0.5 * free) // (4 * max(seg_floats, 1)))))
+    with _Record.lock:
+        room = min(RECORD_SHARE * total - _Record.held.get(device, 0), FREE_SHARE * free)
+    return max(0, min(n_seg, int(room // (4 * max(seg_floats, 1)))))
+
+
+def _take_records(segments, seg_floats: int, device) -> dict:
+    """Memory for the records of the last of the given segments, as many as may be kept."""
+    out = {}
+    with _Record.lock:
+        keep = _kept_segments(len(segments), seg_floats, device)
+        for s in segments[len(segments) - keep:][::-1]:
+            try:
+                out[s] = _Record(seg_floats, device)
+            except torch.OutOfMemoryError:      # held by others in the meantime
+                break
+    return out
 
 
 def _record_floats(disk: Disk, seg_steps: int, noise) -> int:
@@ -78,15 +113,13 @@ class CoreTrajectory(torch.autograd.Function):
         m = m0.detach().clone().contiguous()
         ckpts = [m.clone()]
         cores = [disk.vortex_core_position(m, lambda_ex_nm)]
-        recs = [None] * n_seg
-        floats = _record_floats(disk, seg_steps, noise)
-        keep = 0
+        recs = {}
         if grad_enabled and any(ctx.needs_input_grad) and seg_steps > 0:
-            keep = _kept_segments(n_seg, floats, m.device)
+            recs = _take_records([s for s in range(n_seg) if _explicit_steps(noise, s, seg_steps)],
+                                 _record_floats(disk, seg_steps, noise), m.device)
         for s in range(n_seg):
-            if s >= n_seg - keep and _explicit_steps(noise, s, seg_steps):
-                recs[s] = torch.empty(floats, dtype=torch.float32, device=m.device)
-                _record(disk, m, seg_steps, prm, noise, s, recs[s])
+            if s in recs:
+                _record(disk, m, seg_steps, prm, noise, s, recs[s].data)
             elif noise is None:
                 disk.rk4_step(m, seg_steps, prm)
             else:
@@ -109,8 +142,10 @@ class CoreTrajectory(torch.autograd.Function):
         rec = None
         disk.core_position_vjp(ctx.ckpts[-1], ctx.lam, ctx.cores[-1], grad_rc[-1], ybar)
         for s in reversed(range(ctx.n_seg)):
-            cur, ctx.recs[s] = ctx.recs[s], None          # given back once read; a second backward pass recomputes it
-            if cur is None:
+            kept = ctx.recs.pop(s, None)                  # given back once read; a second backward pass recomputes it
+            if kept is not None:
+                cur = kept.data
+            else:
                 if rec is None:
                     rec = torch.empty(_record_floats(disk, seg, ctx.noise), dtype=torch.float32, device=ybar.device)
                 cur = rec

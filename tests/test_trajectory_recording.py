@@ -63,3 +63,50 @@ def test_a_segment_on_the_step_counter_is_stepped_plainly(step0, counter):
     run(disk, noise=(7, step0, 0))
     want = [("heun_step" if s == counter else "heun_record", step0 + 2 * s) for s in range(3)]
     assert disk.calls == want
+
+
+def test_live_trajectories_share_one_bound(monkeypatch):
+    """With room for five records in all, three live trajectories of three segments keep
+    three, two and none; what a backward pass or a dropped graph gives back is used again."""
+    one = 4 * 8 * 2 * Counting.state_size
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (1 << 40, 16 * 5 * one + 16))
+    disks = [Counting() for _ in range(3)]
+    paths = [run(d) for d in disks]
+    assert [d.count("rk4_record") for d in disks] == [3, 2, 0]
+    assert [d.count("rk4_step") for d in disks] == [0, 1, 3]
+    paths[1].sum().backward()                                  # the segment that was not kept is recorded again
+    assert disks[1].count("rk4_vjp") == 3 and disks[1].count("rk4_record") == 3
+    again = Counting()
+    kept = run(again)
+    assert again.count("rk4_record") == 2
+    del paths[0], kept                                         # no backward pass: the graph's records go with it
+    last = Counting()
+    run(last)
+    assert last.count("rk4_record") == 3
+
+
+def test_little_free_memory_is_left_alone(monkeypatch):
+    one = 4 * 8 * 2 * Counting.state_size
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (16 * one, 1 << 40))
+    disk = Counting()
+    run(disk)
+    assert disk.count("rk4_record") == 2                       # an eighth of what is free
+
+
+def test_records_that_cannot_be_allocated_are_recomputed(monkeypatch):
+    real, given = torch.empty, []
+
+    def empty(*a, **kw):
+        if a == (8 * 2 * Counting.state_size,):
+            given.append(a)
+            if len(given) == 2:
+                raise torch.OutOfMemoryError("none left")
+        return real(*a, **kw)
+    monkeypatch.setattr(torch, "empty", empty)
+    before = sum(adjoint._Record.held.values())
+    disk = Counting()
+    rc = run(disk)
+    assert disk.calls == [("rk4_step", None)] * 2 + [("rk4_record", None)]
+    rc.sum().backward()
+    assert disk.count("rk4_vjp") == 3
+    assert sum(adjoint._Record.held.values()) == before
