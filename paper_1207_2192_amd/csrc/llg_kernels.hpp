@@ -1567,7 +1567,8 @@ constexpr int halo_floats(int PMAX) {
 // register budget the compiler must meet; a plan tuned for an integrator then
 // holds the relaxation too); the other modes take what they need.  Workgroups of
 // two unit groups have a CU to themselves (six wavefronts, two on a SIMD), so
-// their instances may use 256 registers and need no scratch memory.
+// their instances may use 256 registers: 145-239 without scratch memory (the series
+// instances of radix-8 plans 256, with 4 and 14 spilled).
 constexpr int min_waves_per_simd(int mode, int UG) {
     return mode == MODE_RK4 || mode == MODE_HEUN || mode == MODE_RELAX ? (UG == 2 ? 2 : 3) : 1;
 }

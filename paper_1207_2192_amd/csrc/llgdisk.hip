@@ -288,6 +288,24 @@ void allow_dynamic_lds(const void* k) {
     (void)hipGetLastError();
 }
 
+// Workgroups of one kernel instance that a plan may count on per CU.  Of several
+// unit groups: one, whatever the occupancy query says.  When the integrators of two
+// unit groups were compiled for three wavefronts a SIMD (168 registers, some scratch
+// memory), plans with two such workgroups on a CU ran out the barrier's poll budget
+// where a disk's workgroups shared an XCD (40 on its 32 CUs, and 33); why is not
+// shown.  Today's integrators of two unit groups may use 256 registers and have no
+// scratch memory; those of P = 512 and the adjoints still fit twice by the query (145 to
+// 165 registers), and stay single for the same reason.  Nor do two pay: CUs that carry
+// two next to CUs that carry one hold their disks up (16 disks of R = 40 nm: 43.5 us
+// per RK4 step on 144 workgroups, 68.9 on 272; 64 replicas of R = 250 nm: 377 us per
+// Heun step on 512 against 293 with four unit groups on 256).
+int workgroups_per_cu(const void* k, int UG, unsigned dyn, int* out) {
+    if (dyn) allow_dynamic_lds(k);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(out, k, WG_THREADS * UG, dyn));
+    if (UG > 1) *out = std::min(*out, 1);
+    return 0;
+}
+
 // Workgroups of the given shape that the kernels of every mode in `modes` (bit
 // mask) can keep co-resident; the integrator kernels carry `onchip_lds` bytes of dynamic LDS (the spectra of on-chip disks).
 int max_coresident_workgroups(int UG, int RSEL, int PMAX, int* out, unsigned modes = ALL_MODES,
@@ -300,19 +318,10 @@ int max_coresident_workgroups(int UG, int RSEL, int PMAX, int* out, unsigned mod
         if (!(modes & (1u << mode))) continue;
         const void* k = persistent_kernel(mode, UG, RSEL, PMAX);
         if (!k) return fail(LLG_EUNSUPPORTED, "no kernel instance for this launch shape");
-        int b = 0;
-        const unsigned dyn = on_chip_instance(mode, UG) ? onchip_lds : 0;
-        if (dyn) allow_dynamic_lds(k);
-        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, WG_THREADS * UG, dyn));
+        int b = 0, rc = workgroups_per_cu(k, UG, on_chip_instance(mode, UG) ? onchip_lds : 0, &b);
+        if (rc) return rc;
         per_cu = std::min(per_cu, b);
     }
-    // Workgroups of several unit groups: one per CU, whatever the query says.  Two of two unit groups (three
-    // wavefronts on a SIMD, 504 of its 512 registers a lane, scratch memory) were not held where a disk's
-    // workgroups shared an XCD: 40 on the 32 CUs of one, and 33, waited for each other past the barrier's poll
-    // budget.  Nor do two pay: CUs that carry two next to CUs that carry one hold their disks up (16 disks of
-    // R = 40 nm: 43.5 us per RK4 step on 144 workgroups, 68.9 on 272; 64 replicas of R = 250 nm: 377 us per
-    // Heun step on 512 against 293 with four unit groups on 256).
-    if (UG > 1) per_cu = std::min(per_cu, 1);
     *out = ncu * per_cu;
     return 0;
 }
@@ -856,8 +865,8 @@ int launch(llg_disk h, int mode, float* m, float* out, long long nsteps, unsigne
             int dev = 0, ncu = 0, b = 0;
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-            if (dyn) allow_dynamic_lds(k);
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, WG_THREADS * h->UG, dyn));
+            int rc = workgroups_per_cu(k, h->UG, dyn, &b);
+            if (rc) return rc;
             if (h->n_wg > ncu * b)
                 return fail(LLG_EUNSUPPORTED, "the launch plan (" + std::to_string(h->n_wg) +
                                                   " workgroups) exceeds what the series kernel keeps co-resident (" +
