@@ -374,14 +374,16 @@ __device__ __forceinline__ int tid() {
 // BAR_LINES), and BAR_LINES lanes poll one each.  Store, barrier and load of another
 // workgroup's value, across the XCDs: one counter 1.47 us at 4 workgroups, 1.75 at
 // 16, 2.44 at 64, 3.37 at 129; sixteen 1.92, 1.85, 1.98 and 2.31 us.  The sixteen
-// lie 256 bytes apart (512 measured the same), and no idle lane polls
-// along: with neighbouring lines and a whole wavefront polling they were slower than
-// one counter for disks of P = 128 on 33 workgroups of one XCD (20 RK4 steps of 4
-// disks of R = 33 nm 733 us with one, 772 with neighbouring lines, 730 now; of 15
-// disks of R = 60 nm 1089, 874 and 823; lone R = 100 nm 1052, 752 and 728).
+// lie 256 bytes apart (512 measured the same), and no idle lane polls along: with
+// neighbouring lines and a whole wavefront polling they were slower than one counter
+// for disks of P = 128 on 33 workgroups of one XCD on most boxes (20 RK4 steps of 4
+// disks of R = 33 nm 733 us with one, 772 with neighbouring lines, 725 now; of 15
+// disks of R = 60 nm 1089, 874 and 812; lone R = 100 nm 1052, 752 and 741).  A
+// single counter's path has no branch of its own: one before the other two paths cost
+// the ragged ensemble 0.8 %.
 constexpr unsigned int SPIN_LIMIT = 1u << 22;   // default budget (seconds of waiting)
 constexpr int BAR_LINES = 16;                   // counters of a disk on many workgroups
-constexpr int LINE_STRIDE = 64, BAR_STRIDE = 32;   // words between them, and between the single ones of the scratch array
+constexpr int LINE_STRIDE = 64, BAR_STRIDE = 32;   // words between them, and from one disk's single counter to the next
 constexpr int bar_lines_for(int G) { return G > 16 ? BAR_LINES : 1; }
 
 __device__ __forceinline__ bool group_barrier(unsigned int* bar, int lines, unsigned int epoch, int g, int G,
@@ -390,36 +392,36 @@ __device__ __forceinline__ bool group_barrier(unsigned int* bar, int lines, unsi
     __syncthreads();
     if (G == 1) return true;
     __shared__ int s_ok;
-    if (lines == 1) {
-        if (threadIdx.x == 0) {
-            __hip_atomic_fetch_add(gbl(bar), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            unsigned int spins = 0;
-            int ok = 1;
-            while (__hip_atomic_load(gbl(bar), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch * G) {
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins > spin_limit) {
-                    ok = 0;
-                    raise_err(err, (int)ERR_BARRIER);
-                    break;
-                }
-            }
-            s_ok = ok;
-        }
-    } else if (threadIdx.x < BAR_LINES) {
+    if (threadIdx.x < 64) {
         const int q = threadIdx.x;
-        if (q == (g & (BAR_LINES - 1)))
-            __hip_atomic_fetch_add(gbl(bar) + q * LINE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // arrivals on counter q after this epoch
-        const unsigned int target = epoch * (unsigned)((G - q + BAR_LINES - 1) / BAR_LINES);
-        const GLOBAL_AS unsigned int* line = gbl(bar) + q * LINE_STRIDE;
+        if (q == 0)
+            __hip_atomic_fetch_add(gbl(bar) + (g & (lines - 1)) * LINE_STRIDE, 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         unsigned int spins = 0;
         int ok = 1;
-        while (true) {
-            const unsigned int seen = __hip_atomic_load(line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__all(seen >= target)) break;
-            if (++spins > spin_limit) {
-                ok = 0;
-                break;
+        if (lines == 1) {
+            if (q == 0) {
+                while (__hip_atomic_load(gbl(bar), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch * G) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (++spins > spin_limit) {
+                        ok = 0;
+                        break;
+                    }
+                }
+            }
+        } else {
+            // arrivals on line q after this epoch
+            if (q < BAR_LINES) {
+                const unsigned int target = epoch * (unsigned)((G - q + BAR_LINES - 1) / BAR_LINES);
+                const GLOBAL_AS unsigned int* line = gbl(bar) + q * LINE_STRIDE;
+                while (true) {
+                    const unsigned int seen = __hip_atomic_load(line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (__all(seen >= target)) break;
+                    if (++spins > spin_limit) {
+                        ok = 0;
+                        break;
+                    }
+                }
             }
         }
         if (q == 0) {

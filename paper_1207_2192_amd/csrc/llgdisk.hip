@@ -544,7 +544,7 @@ int plan(llg_disk h, int UG, int RSEL, const int* wg_per_disk, unsigned modes = 
         DiskDesc& d = h->desc[k];
         d.bar = h->bars + h->n_bars;
         d.bar_lines = bar_lines_for(G[k]);
-        h->n_bars += d.bar_lines * LINE_STRIDE;
+        h->n_bars += d.bar_lines == 1 ? BAR_STRIDE : d.bar_lines * LINE_STRIDE;
         h->dfree(d.part);
         d.part = nullptr;
         if ((rc = h->dalloc(&d.part, (size_t)PART_STRIDE * G[k]))) return rc;
