@@ -137,24 +137,26 @@ __device__ __forceinline__ void bfly_i(float2& a, float2& b, float2 w) {
 struct Twiddle8 {
     float2 w1, w2, w4, w8;
 };
-// From the table, w = tw[e]: all four where a lane keeps them for many transforms
-// (columns), w and w^2 where every transform makes them anew (rows; all four there
-// cost 1-1.7 % of a Heun step).  Products of w alone left the field 7-10 % less
-// accurate than the plain transforms of the smaller sizes would: 1.08e-6 of its norm
-// at D = 250 against 9.8e-7, now 9.1e-7; 8.4e-7, 7.9e-7 and 6.2e-7 at D = 150.
-template <int P>
-__device__ __forceinline__ Twiddle8 table_twiddle8(const float2* tw, int e) {
-    return {tw[e], tw[2 * e], tw[4 * e], tw[e + P / 8]};
-}
+// TAB: all four from the table, w = tw[e]; else by products of w.  With products
+// everywhere the field is 7-10 % less accurate than plain transforms make it (1.08e-6
+// of its norm at D = 250 against 9.8e-7) and the energy 3 %; with the table everywhere
+// 8.8e-7 and as plain, but the reads that the rows make for every transform cost a Heun
+// step of 64 replicas 1-2 %.  So the rows of the integrators use products, where the
+// columns alone bring the field back to 1.00e-6 and below (-4 % to +2 % of plain, D = 130
+// to 250), and all others the table.  (w^4 as the square of w^2 from the table costs the
+// energy, which sees the field's gain, 40 %.)
+template <int P, bool TAB>
 __device__ __forceinline__ Twiddle8 make_twiddle8(const float2* tw, int e) {
+    const float2 w1 = tw[e];
+    if constexpr (TAB) return {w1, tw[2 * e], tw[4 * e], tw[e + P / 8]};
     const float r = 0.70710678118654752440f;
-    const float2 w1 = tw[e], w2 = tw[2 * e];
+    const float2 w2 = cmul(w1, w1);
     return {w1, w2, cmul(w2, w2), make_float2(r * (w1.x + w1.y), r * (w1.y - w1.x))};
 }
 
 // x_k <- sum_j x_j w^j exp(-+2 pi i j k / 8): 72 vector operations against 80 for
-// seven products and a plain transform, and 8 against 24 for the twiddles, which
-// every row transform makes anew, but chains of three dependent ones per step.
+// seven products and a plain transform, and 12 or none against 24 for the twiddles,
+// which every row transform makes anew, but chains of three dependent ones per step.
 // Faster where three wavefronts share a SIMD (the 64 replicas of R = 250 nm,
 // P = 512: 281.4 -> 278 us per Heun step), slower where a wavefront waits for
 // itself (ragged ensemble, P <= 256: 357 -> 366 us per RK4 step), no different in
@@ -243,7 +245,7 @@ __device__ __forceinline__ void stage_twiddles(StageTwiddles<P, R>& st, const fl
     for (int s = 1; s < StageTwiddles<P, R>::NFULL; ++s) {
         const int e = (t & (Ns - 1)) * (P / (Ns * R));
         if constexpr (fft_fused<P, R>()) {
-            st.f[s - 1] = table_twiddle8<P>(tw, e);
+            st.f[s - 1] = make_twiddle8<P, true>(tw, e);
         } else {
             float2 w[R];
             twiddle_powers<R>(tw[e], w);
@@ -258,7 +260,9 @@ __device__ __forceinline__ void stage_twiddles(StageTwiddles<P, R>& st, const fl
 // ZHO: only the outputs below P/2 are needed; the last stage neither computes
 // nor writes the others (buf keeps stale values there).
 // st: precomputed stage twiddles of this lane (or null: computed per stage).
-template <int P, int R, bool INV, bool KEEP = false, bool WGSYNC = true, bool ZHI = false, bool ZHO = false>
+// TAB: the factors of a fused stage come from the table (make_twiddle8).
+template <int P, int R, bool INV, bool KEEP = false, bool WGSYNC = true, bool ZHI = false, bool ZHO = false,
+          bool TAB = true>
 __device__ __forceinline__ void fft_run(float2 (&v)[R], float2* buf, const float2* tw, int t,
                                         const StageTwiddles<P, R>* st = nullptr) {
     constexpr int Tf = P / R;
@@ -274,7 +278,7 @@ __device__ __forceinline__ void fft_run(float2 (&v)[R], float2* buf, const float
             if (s > 0) {
 #pragma unroll
                 for (int j = 0; j < R; ++j) v[j] = buf[padb(t + j * Tf)];
-                fused_dft8<INV>(v, st ? st->f[s - 1] : make_twiddle8(tw, (t & (Ns - 1)) * (P / (Ns * R))));
+                fused_dft8<INV>(v, st ? st->f[s - 1] : make_twiddle8<P, TAB>(tw, (t & (Ns - 1)) * (P / (Ns * R))));
             } else if constexpr (ZHI) {
                 dft8_lo<INV>(v);
             } else {

@@ -165,6 +165,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
     };
 
     // ---- forward transforms along x of the packed rows in LDS; unpack to S
+    constexpr bool TABR = MODE != MODE_RK4 && MODE != MODE_HEUN;   // row twiddles of P = 512 from the table
     auto row_forward_store = [&](int b) {
         float2 v[R];   // columns at or past P/2 (>= D) are zero
 #pragma unroll
@@ -172,7 +173,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
             const int i = t + j * Tf;
             v[j] = (i < D) ? mybuf[padb(i)] : make_float2(0.f, 0.f);
         }
-        fft_run<P, R, false, false, true, true>(v, mybuf, ltw, t);
+        fft_run<P, R, false, false, true, true, false, TABR>(v, mybuf, ltw, t);
         for (int idx = tid<OPQ>(); idx < U * H; idx += NT) {
             int uu, k;
             pair_map(idx, uu, k);
@@ -460,7 +461,7 @@ __device__ __forceinline__ void run_disk(const KArgs& a, const DiskDesc& d, cons
         float2 v[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) v[j] = mybuf[padb(t + j * Tf)];
-        fft_run<P, R, true, false, true, false, true>(v, mybuf, ltw, t);   // only columns < P/2 (>= D) are read
+        fft_run<P, R, true, false, true, false, true, TABR>(v, mybuf, ltw, t);   // only columns < P/2 (>= D) are read
     };
     auto row_inverse = [&](int b) {
         SRow sv[IS];
