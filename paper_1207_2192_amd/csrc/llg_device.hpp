@@ -376,7 +376,7 @@ __device__ __forceinline__ int tid() {
 // 16, 2.44 at 64, 3.37 at 129; sixteen 1.92, 1.85, 1.98 and 2.31 us.  The sixteen
 // lie 256 bytes apart (512 measured the same), and no idle lane polls along: with
 // neighbouring lines and a whole wavefront polling they were slower than one counter
-// for disks of P = 128 on 33 workgroups of one XCD on most boxes (20 RK4 steps of 4
+// for disks of P = 128 on 33 workgroups of one XCD on most cards (20 RK4 steps of 4
 // disks of R = 33 nm 733 us with one, 772 with neighbouring lines, 725 now; of 15
 // disks of R = 60 nm 1089, 874 and 812; lone R = 100 nm 1052, 752 and 741).  A
 // single counter's path has no branch of its own: one before the other two paths cost
